@@ -61,7 +61,7 @@ SCOPES = {"expert-resident": SCOPE_RESIDENT, "fused": SCOPE_FUSED, "fused-local"
 
 
 KERNEL_SOURCES = ("lowrank.hip", "lowrank.h", "device_common.h", "route_device.h",
-                  "resident.hip", "histogram.hip")
+                  "bucket.hip", "bucket.h", "histogram.hip")
 
 
 def kernel_source_digest():

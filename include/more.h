@@ -112,7 +112,7 @@ more_status more_route_lowrank_workspace_size(int64_t T, int32_t h, int32_t r, i
  * The one-launch fused route (r M <= 2^17 with K <= 8, and M <= 1024 at r = 64) computes z
  * inside the routing workgroup, summing the h axis in another order: its logits can differ from
  * the others' in the last bits (selections only where logits tie to rounding); so can those of
- * the single-pass route, which m_chunks = 0 picks for T >= 4096 and M >= 32768.  This entry
+ * the routes that m_chunks = 0 picks for larger expert sets.  This entry
  * point exists for tuning and for tests of these properties.  The wide route ignores m_chunks
  * (any valid value gives the same result).  Its workspace size comes from
  * more_route_lowrank_workspace_size_ex with the same m_chunks (0 bytes for the one-launch
@@ -130,18 +130,19 @@ more_status more_route_lowrank_workspace_size_ex(int64_t T, int32_t h, int32_t r
  * number of expert-axis slices of the expert-resident route, or 0 when the library routes this
  * shape with a route that no m_chunks >= 1 selects: a fused route (expert sets with
  * r * M <= 2^18 and M <= 16384: one workgroup per 64 tokens sweeps all experts) or the
- * single-pass route (T >= 4096 and M >= 32768: one screening sweep over all experts after a
- * prescreen of a quarter of them; see more_route_lowrank_ex) or the wide route. */
+ * single-pass route (T >= 4096 and M >= 32768) or the wide route.  (With m_chunks = 0 both larger
+ * routes make one screening sweep that keeps bucket maxima; the chunk count is what a call with
+ * an explicit m_chunks would take.) */
 more_status more_route_lowrank_plan(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k,
                                     int32_t* m_chunks);
 
 /* The route more_route_lowrank takes for this shape (written to *route, host): one of the
  * MORE_ROUTE_* codes below.  Routes differ in speed and in the summation order of z = x R1 (see
  * more_route_lowrank_ex); every route returns the exact top k of its own fp32 logits. */
-#define MORE_ROUTE_RESIDENT 0    /* z pass; screen, threshold, collect and finalize per chunk  */
+#define MORE_ROUTE_RESIDENT 0    /* z pass; one sweep that keeps bucket maxima, selection       */
 #define MORE_ROUTE_FUSED 1       /* z pass; one fused kernel per 64 tokens over all experts     */
 #define MORE_ROUTE_FUSED_LOCAL 2 /* one launch: the fused kernel also computes z                */
-#define MORE_ROUTE_SINGLE_PASS 3 /* z + prescreen, one collect sweep, finalize (+ histogram)    */
+#define MORE_ROUTE_SINGLE_PASS 3 /* the same, for T >= 4096 and M >= 32768                      */
 #define MORE_ROUTE_WIDE 4        /* z per rank block; exact 3-piece split; fused 3r-wide sweep */
 more_status more_route_lowrank_route(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k,
                                      int32_t* route);

@@ -18,7 +18,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmore.so")
-SOURCES = ["lowrank.hip", "resident.hip", "fullrank.hip", "histogram.hip", "dispatch.hip", "stats.hip", "fullrank_fused.hip",
+SOURCES = ["lowrank.hip", "bucket.hip", "fullrank.hip", "histogram.hip", "dispatch.hip", "stats.hip", "fullrank_fused.hip",
            "backward.hip", "wide.hip",
            "noalloc.hip", "more_api.cpp"]
 ARCH = "gfx950"
@@ -40,7 +40,7 @@ def compile_flags() -> list[str]:
 
 # Per-source extra flags.  The router kernels never see NaN (inputs are finite, masked logits
 # are -inf), so fmaxf/fminf need no NaN quieting.
-EXTRA_FLAGS = {"lowrank.hip": ["-fno-honor-nans"], "resident.hip": ["-fno-honor-nans"]}
+EXTRA_FLAGS = {"lowrank.hip": ["-fno-honor-nans"], "bucket.hip": ["-fno-honor-nans"]}
 
 
 def _compile(src: str) -> str:

@@ -1,0 +1,39 @@
+// Bucket route (bucket.hip): one screening sweep that keeps bucket maxima, then an exact selection
+// from the few buckets that can hold the top k.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+namespace more {
+
+constexpr int32_t kBucketMaxRank = 256;
+constexpr int32_t kBucketMinExperts = 2048;
+constexpr int32_t kBucketMaxExperts = 1 << 24;
+
+struct BucketPlan {
+    int64_t slab;  // tokens per sweep and select launch
+    int32_t nCp;   // floats per token of the coarse maxima
+    size_t off_fine, off_coarse, off_fnorm, off_cnorm, bytes;
+};
+
+struct BucketArgs {
+    const float* z;        // fp32 [T][r]
+    const uint16_t* zhi;   // bf16(z) [T][r]
+    const float* cz;       // screening scale [T]
+    const uint16_t* R2t;
+    int64_t T;
+    int32_t r, M, k;
+    int32_t* hist;         // nullable; cleared
+    int32_t* idx;
+    float *gate, *topval;  // topval nullable
+};
+
+// false when the shape is outside the route's limits.  z_bytes: what the caller keeps beside the
+// route's scratch; the slab is chosen so that both stay within 240 MB where 32 MB allow it.
+bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t z_bytes, BucketPlan* plan);
+hipError_t bucket_launch(const BucketPlan& plan, const BucketArgs& a, void* scratch,
+                         hipStream_t stream);
+
+}  // namespace more

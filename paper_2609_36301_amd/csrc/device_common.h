@@ -156,7 +156,7 @@ __device__ __forceinline__ void list_merge(float (&av)[K], int32_t (&ai)[K], con
 // ---------------------------------------------------------------- cross-lane moves
 // The value of x held by lane (lane ^ M).  M = 1 and 2 are DPP quad permutations, M = 4 a
 // half-row mirror followed by a quad reversal (lane i of an 8-lane group reads 7 - (i ^ 3) =
-// i ^ 4); these stay in the VALU instead of going through the LDS crossbar of a general
+// i ^ 4), M = 8 a rotation of the 16-lane row by half; these stay in the VALU instead of going through the LDS crossbar of a general
 // shuffle.  Other M use __shfl_xor.
 template <int M, typename T>
 __device__ __forceinline__ T lane_xor(T x) {
@@ -170,6 +170,8 @@ __device__ __forceinline__ T lane_xor(T x) {
     } else if constexpr (M == 4) {
         const int h = __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, false);  // row_half_mirror
         r = __builtin_amdgcn_mov_dpp(h, 0x1B, 0xF, 0xF, false);             // quad_perm [3,2,1,0]
+    } else if constexpr (M == 8) {
+        r = __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, false);  // row_ror:8, lane (i + 8) mod 16
     } else {
         r = __shfl_xor(v, M, kWave);
     }
@@ -183,6 +185,21 @@ __device__ __forceinline__ void lane_pair32(float x, float& a, float& b) {
     const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
     a = __builtin_bit_cast(float, (unsigned)r[0]);
     b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+// The same for lanes l and l ^ 16 (permlane16 swap: the odd rows of 16 lanes of the first operand
+// against the even rows of the second).
+__device__ __forceinline__ void lane_pair16(float x, float& a, float& b) {
+    const unsigned v = __builtin_bit_cast(unsigned, x);
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = __builtin_bit_cast(float, (unsigned)r[0]);
+    b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+// The value of x in lane 7 - l of the 8-lane group (for sums already equal within each quad).
+__device__ __forceinline__ float lane_half_mirror(float x) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x141, 0xF, 0xF, false));
 }
 
 // x plus its value in lane l ^ 32.
@@ -203,6 +220,42 @@ __device__ __forceinline__ void list_merge_xor(float (&v)[K], int32_t (&ix)[K]) 
         pi[j] = lane_xor<M>(ix[j]);
     }
     list_merge<K>(v, ix, pv, pi);
+}
+
+// The wave's LDS writes complete before any of its lanes reads them back (s_waitcnt
+// lgkmcnt(0); the other counters keep their maximum).  Waves of a workgroup exit at different
+// times here, so there is no workgroup barrier.
+__device__ __forceinline__ void wave_lds_sync() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((15) | (3 << 14) | (7 << 4));
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// x sorted descending across the 64 lanes of the wave (lane 0 the largest): bitonic network
+// of 21 compare-exchange stages, partners by lane_xor.
+__device__ __forceinline__ float wave_sort_desc(float x, int lane) {
+#pragma unroll
+    for (int size = 2; size <= 64; size <<= 1) {
+#pragma unroll
+        for (int d = size >> 1; d >= 1; d >>= 1) {
+            float y;
+            switch (d) {
+                case 1: y = lane_xor<1>(x); break;
+                case 2: y = lane_xor<2>(x); break;
+                case 4: y = lane_xor<4>(x); break;
+                case 8: y = lane_xor<8>(x); break;
+                case 16: y = lane_xor<16>(x); break;
+                default: y = lane_xor<32>(x); break;
+            }
+            // within blocks of `size`, descending where (lane & size) == 0 (the last stage
+            // has size 64: all descending); the lower lane of a pair keeps the larger value
+            const bool desc = (lane & size) == 0 || size == 64;
+            const bool lower = (lane & d) == 0;
+            x = (lower == desc) ? fmaxf(x, y) : fminf(x, y);
+        }
+    }
+    return x;
 }
 
 // softmax over the first k entries of a sorted list, then store idx / gate / topval row.

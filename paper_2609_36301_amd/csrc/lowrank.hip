@@ -2,10 +2,13 @@
 // T x M logits (Appendix "Pseudocode", inference algorithm; MoRE layer in "Preliminaries").
 //
 // Routes of one call (chosen per shape by lowrank_make_plan):
-//   expert-resident  zpass (z = x R1, fp32, and the group norms of R2t's rows unless the screen
-//                    kernel takes them) [+ zreduce when the h axis is split over workgroups],
-//                    then screen, threshold, collect and finalize kernels; screen and collect
-//                    workgroups hold one chunk of the expert axis in LDS;
+//   bucket           zpass (z = x R1, fp32) [+ zreduce when the h axis is split over workgroups], then
+//                    the sweep and select kernels of bucket.hip (reported as the expert-resident
+//                    route, or as the single-pass route for many tokens and experts);
+//   expert-resident  an explicit chunk count (and fewer than 2048 experts outside the fused routes):
+//                    zpass (with the group norms of R2t's rows unless the screen kernel takes
+//                    them), then screen, threshold, collect and finalize kernels; screen and
+//                    collect workgroups hold one chunk of the expert axis in LDS;
 //   fused            zpass, then one fused_route_kernel: a workgroup of 64 tokens sweeps the
 //                    whole expert axis (operands streamed from L2) through the same four steps;
 //   local            one fused_local_kernel: the fused workgroup also computes z and one norm
@@ -1160,48 +1163,27 @@ bool lowrank_make_plan(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k, in
     q.off_cand = off;
     off += route_ws * align256((size_t)T * q.cap * sizeof(int32_t));
     q.workspace_bytes = q.local ? 0 : off;
-    // Single-pass route: the library's choice for expert sets of at least 32768 (below that the
-    // resident route's two sweeps cost less than the single pass's records) and enough tokens to
-    // fill the chip with 64-token workgroups of the z pass.  Its prescreen assumes that its tiles
-    // lie below M (32 sub_tiles <= M, true at these sizes).
-    q.single_pass = m_chunks == 0 && !q.fused && T >= 4096 && M >= 32768 && M <= (1 << 24) &&
-                    q.K <= 16 && h < (1 << 24) &&
-                    32 * ((Mt + 3) / 4 > 8 ? (Mt + 3) / 4 : 8) <= M;
-    if (q.single_pass) {
-        q.ntb = (int32_t)((T + 511) / 512);  // collect blocks of 512 tokens
-        int64_t C = (Mt + emax_tiles - 1) / emax_tiles;
-        const int64_t want = (256 + q.ntb - 1) / q.ntb;
-        if (C < want) C = want < Mt ? want : Mt;
-        q.chunks = (int32_t)(C < 1024 ? C : 1024);
-        while ((Mt + q.chunks - 1) / q.chunks > emax_tiles) q.chunks *= 2;
-        int64_t Sp = 256 / q.chunks;
-        if (Sp < 1) Sp = 1;
-        if (Sp > q.ntb) Sp = q.ntb;
-        q.splits = (int32_t)Sp;
-        // prescreen: a quarter of the expert tiles, at least 8 (one per wave); an eighth leaves
-        // a looser threshold and more records for collect and finalize (2% slower on fine_grained)
-        int64_t st = (Mt + 3) / 4;
-        if (st < 8) st = 8;
-        if (st > Mt) st = Mt;
-        q.sub_tiles = (int32_t)st;
-        q.cap = M > 16384 ? 1024 : 512;  // records per token (more on large expert sets)
-        q.slots = 16;
-        size_t o = 0;
-        q.off_z = o;
-        o += align256((size_t)T * r * sizeof(float));
-        q.off_zhi = o;
-        o += align256((size_t)T * r * sizeof(uint16_t));
-        q.off_cz = o;
-        o += align256((size_t)T * sizeof(float));
-        q.off_theta0 = o;
-        o += align256((size_t)T * sizeof(float));
-        q.off_count = o;
-        o += align256((size_t)T * sizeof(int32_t));
-        q.off_rec = o;
-        o += align256((size_t)T * q.cap * 2 * sizeof(int32_t));
-        q.off_scratch = o;
-        o += align256(collect_scratch_bytes((int64_t)q.chunks * q.splits, q.slots));
-        q.workspace_bytes = o;
+    // Bucket route: the library's choice wherever no fused route applies (one sweep over the expert
+    // axis instead of the resident route's two).  Its scratch follows z, z_hi and c.  The workspace
+    // is never smaller than what the lists of candidates would take (512 per token; 1024 with their
+    // bounds, and the entry slots of the workgroups, for many tokens and experts): the shapes
+    // that more_route_lowrank_noalloc takes and refuses are a contract of their own.
+    q.off_bk = q.off_top;
+    q.bucket = m_chunks == 0 && !q.fused && bucket_make_plan(T, r, M, k, q.off_bk, &q.bk);
+    q.single_pass = q.bucket && T >= 4096 && M >= 32768;
+    if (q.bucket) {
+        size_t lists = off;
+        if (q.single_pass) {
+            int64_t C = (Mt + emax_tiles - 1) / emax_tiles;
+            const int64_t want = (256 + q.ntb - 1) / q.ntb;
+            if (C < want) C = want;
+            const int64_t S = C > 256 ? 1 : (256 / C < q.ntb ? 256 / C : q.ntb);
+            lists = align256((size_t)T * r * 4) + align256((size_t)T * r * 2) +
+                    3 * align256((size_t)T * 4) + align256((size_t)T * 8192) +
+                    (size_t)(C * S) * 278528;
+        }
+        const size_t need = q.off_bk + q.bk.bytes;
+        q.workspace_bytes = need > lists ? need : lists;
     }
     *p = q;
     return true;
@@ -1216,7 +1198,7 @@ static void launch_zpass(const LowrankPlan& p, const uint16_t* x, const uint16_t
     // group-norm workgroups, unless the expert-resident route runs one token split: then its
     // screen kernel computes the norms from its LDS chunk (each chunk is loaded once)
     const int64_t nblocks =
-        p.fused || p.splits > 1
+        !p.bucket && (p.fused || p.splits > 1)
             ? (((int64_t)M + 31) / 32 * 32 * (r / 8) + 256 * kGroupNormBlocks - 1) /
                   (256 * kGroupNormBlocks)
             : 0;
@@ -1359,29 +1341,6 @@ hipError_t lowrank_launch(const LowrankPlan& p, const uint16_t* x, const uint16_
         return hipGetLastError();
     }
     char* ws = static_cast<char*>(workspace);
-    if (p.single_pass) {
-        SinglePassArgs s;
-        s.x = x;
-        s.R1t = R1t;
-        s.R2t = R2t;
-        s.T = (int32_t)T;
-        s.h = h;
-        s.r = r;
-        s.M = M;
-        s.k = k;
-        s.z = reinterpret_cast<float*>(ws + p.off_z);
-        s.zhi = reinterpret_cast<uint16_t*>(ws + p.off_zhi);
-        s.cz = reinterpret_cast<float*>(ws + p.off_cz);
-        s.theta0 = reinterpret_cast<float*>(ws + p.off_theta0);
-        s.count = reinterpret_cast<int32_t*>(ws + p.off_count);
-        s.rec = reinterpret_cast<int2*>(ws + p.off_rec);
-        s.scratch = ws + p.off_scratch;
-        s.hist = counts;
-        s.idx = idx;
-        s.gate = gate;
-        s.topval = topval;
-        return single_pass_launch(p, s, st);
-    }
     float* zparts = reinterpret_cast<float*>(ws + p.off_zparts);
     RouteArgs a;
     a.z = reinterpret_cast<float*>(ws + p.off_z);
@@ -1413,6 +1372,10 @@ hipError_t lowrank_launch(const LowrankPlan& p, const uint16_t* x, const uint16_
         hipLaunchKernelGGL(zreduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
                            zparts, const_cast<float*>(a.z), a.zhi, a.cz, (int32_t)T, r,
                            p.hsplit);
+    }
+    if (p.bucket) {
+        const BucketArgs b{a.z, a.zhi, a.cz, R2t, T, r, M, k, counts, idx, gate, topval};
+        return bucket_launch(p.bk, b, ws + p.off_bk, st);
     }
     bool ok = false;
     switch (p.RC) {

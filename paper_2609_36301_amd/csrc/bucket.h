@@ -25,6 +25,8 @@ struct BucketArgs {
     const uint16_t* R2t;
     int64_t T;
     int32_t r, M, k;
+    bool pieces;           // exact logits as sums of eight products added up (closer to exact at long
+                           // ranks), else as one chain, bit for bit as the resident route's
     int32_t* hist;         // nullable; cleared
     int32_t* idx;
     float *gate, *topval;  // topval nullable

@@ -416,7 +416,8 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     const uint16_t* __restrict__ R2t, const uint16_t* __restrict__ fine,
     const float* __restrict__ coarse, const float* __restrict__ fnorm,
     const float* __restrict__ cnorm, int32_t T, int32_t Tp, int32_t nCp, int32_t r, int32_t M,
-    int32_t k, int32_t* __restrict__ idx, float* __restrict__ gate, float* __restrict__ topval) {
+    int32_t k, bool pieces, int32_t* __restrict__ idx, float* __restrict__ gate,
+    float* __restrict__ topval) {
     using C = SelectCfg<K, COOP>;
     constexpr int LPT = C::LPT, TPW = C::TPW, NCAND = C::NCAND, TOKENS = C::TOKENS;
     constexpr int LANES = COOP ? kSelThreads : LPT;  // lanes of a token in all
@@ -722,7 +723,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
             const int i = i0 + gl;
             const int32_t e = i < n3 ? list3[j][i] : 0;
             const uint16_t* ur = R2t + (uint32_t)e * (uint32_t)r;
-            float l = 0.0f;  // rank entries in increasing order
+            float l = 0.0f;  // rank entries in increasing order (pieces: sums of eight, added up)
             for (int c0 = 0; c0 < r; c0 += 8 * ES) {
                 const int ns = r - c0 < 8 * ES ? (r - c0) / 8 : ES;
                 bf16x8 u[ES];
@@ -733,10 +734,12 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
                     if (g < ns) {
                         const f32x4 za = *reinterpret_cast<const f32x4*>(&zrow[j][c0 + 8 * g]);
                         const f32x4 zb = *reinterpret_cast<const f32x4*>(&zrow[j][c0 + 8 * g + 4]);
+                        float p = pieces ? 0.0f : l;
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) l = fmaf(za[t], (float)u[g][t], l);
+                        for (int t = 0; t < 4; ++t) p = fmaf(za[t], (float)u[g][t], p);
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) l = fmaf(zb[t], (float)u[g][4 + t], l);
+                        for (int t = 0; t < 4; ++t) p = fmaf(zb[t], (float)u[g][4 + t], p);
+                        l = pieces ? l + p : p;
                     }
                 }
             }
@@ -793,8 +796,10 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
             float l = 0.0f;
             for (int s = 0; s < r; s += 8) {
                 const bf16x8 u = load_bf16x8(ur + s);
+                float p = pieces ? 0.0f : l;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) l = fmaf(zrow[jt][s + i], (float)u[i], l);
+                for (int i = 0; i < 8; ++i) p = fmaf(zrow[jt][s + i], (float)u[i], p);
+                l = pieces ? l + p : p;
             }
             if (better(l, e, lv[K - 1], ix[K - 1])) list_insert<K>(lv, ix, l, e);
         }
@@ -905,7 +910,7 @@ void launch_select(const BucketArgs& a, int64_t t0, int32_t T, int32_t Tp, int32
     hipLaunchKernelGGL((bucket_select_kernel<SEG, NS, K, COOP>), dim3((unsigned)((T + TOK - 1) / TOK)),
                        dim3(kSelThreads), 0, st, a.z + t0 * a.r, a.zhi + t0 * a.r, a.cz + t0,
                        a.R2t, reinterpret_cast<const uint16_t*>(fine), coarse, fnorm, cnorm, T, Tp,
-                       nCp, a.r, a.M, a.k, a.idx + t0 * a.k, a.gate + t0 * a.k,
+                       nCp, a.r, a.M, a.k, a.pieces, a.idx + t0 * a.k, a.gate + t0 * a.k,
                        a.topval ? a.topval + t0 * a.k : nullptr);
 }
 

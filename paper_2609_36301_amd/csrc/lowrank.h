@@ -61,8 +61,14 @@ hipError_t fullrank_launch(const FullrankPlan& plan, const uint16_t* x, const ui
                            int64_t T, int32_t h, int32_t M, int32_t k, int32_t* idx, float* gate,
                            float* topval, void* workspace, hipStream_t stream, int* blas_status);
 
-// z = x R1 alone, fp32 [T][r] at z, for callers other than the routes (the h-split partials
-// and the z_hi / error-scale byproducts of the z pass go to scratch).
+// z = x R1, fp32 [T][r] at z, with z_hi = bf16(z) [T][r] and the screening scale cz [T], for callers other
+// than the routes; r a multiple of 16 up to 256.  scratch: zpass_workspace_bytes (the h-split
+// partials).
+size_t zpass_workspace_bytes(int64_t T, int32_t h, int32_t r);
+hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
+                        float* z, uint16_t* zhi, float* cz, void* scratch, hipStream_t stream);
+
+// z alone (z_hi and the scale go to the scratch as well).
 size_t zonly_workspace_bytes(int64_t T, int32_t h, int32_t r);
 hipError_t zonly_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
                         float* z, void* scratch, hipStream_t stream);

@@ -292,6 +292,56 @@ __global__ __launch_bounds__(256) void zreduce_kernel(const float* __restrict__ 
     }
 }
 
+// The same for any r (a multiple of 16 up to 256): a wave per token, lane l taking the rank entries
+// l, l + 64, ...
+__global__ __launch_bounds__(256) void zreduce_wide_kernel(const float* __restrict__ zparts,
+                                                           float* __restrict__ z,
+                                                           uint16_t* __restrict__ zhi,
+                                                           float* __restrict__ cz, int32_t T,
+                                                           int32_t r, int32_t splits) {
+    const int lane = threadIdx.x & 63;
+    const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (t >= T) return;  // wave-uniform
+    const int64_t n = (int64_t)T * r;
+    float hi2 = 0.0f, lo2 = 0.0f;
+    for (int j = lane; j < r; j += 64) {
+        const int64_t i = t * r + j;
+        float s = 0.0f;
+        int p = 0;
+        for (; p + 16 <= splits; p += 16) {  // 16 loaded before they are added, in split order
+            float v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = zparts[(int64_t)(p + q) * n + i];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s += v[q];
+        }
+        for (; p < splits; ++p) s += zparts[(int64_t)p * n + i];
+        const __bf16 hb = (__bf16)s;
+        const float hf = (float)hb, lf = s - hf;
+        hi2 = fmaf(hf, hf, hi2);
+        lo2 = fmaf(lf, lf, lo2);
+        z[i] = s;
+        zhi[i] = __builtin_bit_cast(uint16_t, hb);
+    }
+    for (int m = 1; m < 64; m <<= 1) {
+        hi2 += __shfl_xor(hi2, m, kWave);
+        lo2 += __shfl_xor(lo2, m, kWave);
+    }
+    if (lane == 0) cz[t] = screen_scale(lo2, hi2, r);
+}
+
+static void launch_zreduce(const float* zparts, float* z, uint16_t* zhi, float* cz, int64_t T,
+                           int32_t r, int32_t splits, hipStream_t st) {
+    if (r == 16 || r == 32 || r == 64) {
+        const int64_t n = T * r;
+        hipLaunchKernelGGL(zreduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                           zparts, z, zhi, cz, (int32_t)T, r, splits);
+    } else {
+        hipLaunchKernelGGL(zreduce_wide_kernel, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, st,
+                           zparts, z, zhi, cz, (int32_t)T, r, splits);
+    }
+}
+
 // Screening sweep.  For each accumulator group q of a tile the lane forms the lower bound
 // max_{e in group} s_e - c N_g (attained by one expert of the group) and keeps the maxima of
 // these bounds in L = 4U buckets (group q of tile t goes to bucket 4 (t mod U) + q).  The
@@ -1286,44 +1336,49 @@ static bool dispatch_local_k(const LowrankPlan& p, const uint16_t* x, const uint
     return false;
 }
 
-size_t zonly_workspace_bytes(int64_t T, int32_t h, int32_t r) {
+size_t zpass_workspace_bytes(int64_t T, int32_t h, int32_t r) {
     int32_t sps, hs;
     zpass_split(T, h, &sps, &hs);
-    return (hs > 1 ? align256((size_t)hs * T * r * sizeof(float)) : 0) +
-           align256((size_t)T * r * sizeof(uint16_t)) + align256((size_t)T * sizeof(float));
+    return hs > 1 ? align256((size_t)hs * T * r * sizeof(float)) : 0;
+}
+
+hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
+                        float* z, uint16_t* zhi, float* cz, void* scratch, hipStream_t st) {
+    int32_t sps, hs;
+    zpass_split(T, h, &sps, &hs);
+    float* zparts = hs > 1 ? static_cast<float*>(scratch) : z;
+    const int64_t zblocks = (T + kZTokens - 1) / kZTokens;
+    const dim3 grid((unsigned)(zblocks * hs));  // no group-norm workgroups
+    constexpr int D = 2;
+    // tiles of 32 rank rows: 1, 2, 4 or 8 (rows past r are computed and dropped)
+#define MORE_ZPASS(RT)                                                                           \
+    hipLaunchKernelGGL((zpass_kernel<RT, D>), grid, dim3(256), 0, st, x, R1t, zparts, (int32_t)T, \
+                       h, r, sps, nullptr, 0, (int32_t)zblocks, hs, nullptr, zhi, cz)
+    if (r <= 32)
+        MORE_ZPASS(1);
+    else if (r <= 64)
+        MORE_ZPASS(2);
+    else if (r <= 128)
+        MORE_ZPASS(4);
+    else
+        MORE_ZPASS(8);
+#undef MORE_ZPASS
+    if (hs > 1) launch_zreduce(zparts, z, zhi, cz, T, r, hs, st);
+    return hipGetLastError();
+}
+
+size_t zonly_workspace_bytes(int64_t T, int32_t h, int32_t r) {
+    return zpass_workspace_bytes(T, h, r) + align256((size_t)T * r * sizeof(uint16_t)) +
+           align256((size_t)T * sizeof(float));
 }
 
 hipError_t zonly_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
                         float* z, void* scratch, hipStream_t st) {
-    int32_t sps, hs;
-    zpass_split(T, h, &sps, &hs);
     char* s = static_cast<char*>(scratch);
-    float* zparts = hs > 1 ? reinterpret_cast<float*>(s) : z;
-    const size_t o1 = hs > 1 ? align256((size_t)hs * T * r * sizeof(float)) : 0;
-    uint16_t* zhi = reinterpret_cast<uint16_t*>(s + o1);
-    float* cz = reinterpret_cast<float*>(s + o1 + align256((size_t)T * r * sizeof(uint16_t)));
-    const int64_t zblocks = (T + kZTokens - 1) / kZTokens;
-    const dim3 grid((unsigned)(zblocks * hs));  // no group-norm workgroups
-    constexpr int D = 2;
-    switch ((r / 16 + 1) / 2) {
-        case 1:
-            hipLaunchKernelGGL((zpass_kernel<1, D>), grid, dim3(256), 0, st, x, R1t, zparts,
-                               (int32_t)T, h, r, sps, nullptr, 0, (int32_t)zblocks, hs, nullptr,
-                               zhi, cz);
-            break;
-        case 2:
-            hipLaunchKernelGGL((zpass_kernel<2, D>), grid, dim3(256), 0, st, x, R1t, zparts,
-                               (int32_t)T, h, r, sps, nullptr, 0, (int32_t)zblocks, hs, nullptr,
-                               zhi, cz);
-            break;
-        default: return hipErrorInvalidValue;
-    }
-    if (hs > 1) {
-        const int64_t n = T * r;
-        hipLaunchKernelGGL(zreduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                           zparts, z, zhi, cz, (int32_t)T, r, hs);
-    }
-    return hipGetLastError();
+    const size_t o1 = zpass_workspace_bytes(T, h, r);
+    const size_t o2 = o1 + align256((size_t)T * r * sizeof(uint16_t));
+    return zpass_launch(x, R1t, T, h, r, z, reinterpret_cast<uint16_t*>(s + o1),
+                        reinterpret_cast<float*>(s + o2), s, st);
 }
 
 hipError_t lowrank_launch(const LowrankPlan& p, const uint16_t* x, const uint16_t* R1t,
@@ -1368,13 +1423,10 @@ hipError_t lowrank_launch(const LowrankPlan& p, const uint16_t* x, const uint16_
         default: return hipErrorInvalidValue;
     }
     if (p.hsplit > 1) {
-        const int64_t n = T * r;
-        hipLaunchKernelGGL(zreduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                           zparts, const_cast<float*>(a.z), a.zhi, a.cz, (int32_t)T, r,
-                           p.hsplit);
+        launch_zreduce(zparts, const_cast<float*>(a.z), a.zhi, a.cz, T, r, p.hsplit, st);
     }
     if (p.bucket) {
-        const BucketArgs b{a.z, a.zhi, a.cz, R2t, T, r, M, k, counts, idx, gate, topval};
+        const BucketArgs b{a.z, a.zhi, a.cz, R2t, T, r, M, k, false, counts, idx, gate, topval};
         return bucket_launch(p.bk, b, ws + p.off_bk, st);
     }
     bool ok = false;

@@ -139,10 +139,11 @@ more_status more_route_lowrank_ex(const uint16_t* x, const uint16_t* R1t, const 
         more::WidePlan w;
         if (!more::wide_make_plan(T, h, r, M, k, &w)) return MORE_ERR_INVALID_ARG;
         if (!workspace || workspace_bytes < w.workspace_bytes) return MORE_ERR_WORKSPACE;
-        if (more::wide_launch(w, x, R1t, R2t, T, h, r, M, k, idx, gate, topval, workspace, st) !=
-            hipSuccess)
+        if (more::wide_launch(w, x, R1t, R2t, T, h, r, M, k, idx, gate, topval, counts, workspace,
+                              st) != hipSuccess)
             return MORE_ERR_HIP;
-        if (counts) return from_hip(more::histogram_launch(idx, T * (int64_t)k, M, counts, st));
+        if (counts)
+            return from_hip(more::histogram_launch(idx, T * (int64_t)k, M, counts, st, w.bucket));
         return MORE_OK;
     }
     more::LowrankPlan p;

@@ -13,11 +13,11 @@ namespace more {
 constexpr int32_t kWideMaxRank = 256;
 
 struct WidePlan {
-    int32_t nblocks;      // rank-column blocks of z = x R1, each 64, 32 or 16 columns wide
-    int32_t j0[8], w[8];  // first column and width of each block (r <= 256: at most 6 blocks)
-    FusedFullrankPlan ff; // the fused sweep over the 3r-wide split of z
+    int32_t bucket;       // 1: the bucket route's sweep and selection (bucket.hip)
+    BucketPlan bk;
+    FusedFullrankPlan ff; // else the fused sweep over the 3r-wide split of z
     bool stack;           // r not a multiple of 64: R2t rows stacked three times (W3)
-    size_t off_z, off_zscratch, off_zs, off_w3, off_ff, workspace_bytes;
+    size_t off_z, off_zscratch, off_zhi, off_cz, off_bk, off_zs, off_w3, off_ff, workspace_bytes;
 };
 
 // The wide route serves (r, k) exactly when the register-tiled routes do not.
@@ -31,9 +31,10 @@ hipError_t fullrank_fused_launch_periodic(const FusedFullrankPlan& plan, const u
                                           const uint16_t* Wt, int32_t ldw, int64_t T, int32_t h,
                                           int32_t M, int32_t k, int32_t* idx, float* gate,
                                           float* topval, void* workspace, hipStream_t stream);
+// counts (nullable) is cleared by the launch when plan.bucket is set.
 hipError_t wide_launch(const WidePlan& plan, const uint16_t* x, const uint16_t* R1t,
                        const uint16_t* R2t, int64_t T, int32_t h, int32_t r, int32_t M, int32_t k,
-                       int32_t* idx, float* gate, float* topval, void* workspace,
+                       int32_t* idx, float* gate, float* topval, int32_t* counts, void* workspace,
                        hipStream_t stream);
 
 }  // namespace more

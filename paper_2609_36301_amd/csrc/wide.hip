@@ -2,20 +2,16 @@
 // paper's rank sweeps that the register-tiled routes do not hold (r a multiple of 16 up to 256,
 // Section "Routing expressivity") and for 17 <= k <= 32.
 //
-// Three launches in sequence on the caller's stream:
-//   1. z = x R1 in fp32, by the z pass of the other routes, run once per block of 64, 32 or 16
-//      rank columns (a block's columns are independent rows of the contraction, so z is the
-//      same as from one pass over all r columns);
-//   2. z is split into three bfloat16 pieces per element whose sum is z exactly, stored as the
-//      rows [z_hi | z_mid | z_lo] of a 3r-wide operand; when r is not a multiple of 64 the rows
-//      of R2t are stacked three times into a matching [M][3r] operand, otherwise the sweep
-//      reads each 64-wide chunk of R2t for all three pieces;
-//   3. the fused standard router sweeps that pair: its fp32 logits are sums of exact bf16
-//      products, i.e. the fp32 dot products of the fp32 z with the bfloat16 expert rows up to
-//      the summation order, and it returns their exact top k (ties to the smaller id), the
-//      softmax over the k and, optionally, the selected logits.
-// The executed matrix work is three times the algorithmic z R2; the route trades that for
-// kernels that keep every rank width and list length in registers without new tilings.
+// 1. z = x R1 in fp32, with z_hi = bf16(z) and the screening scale, by the z pass of the other routes
+//    (up to 256 rank columns in one launch);
+// 2. from kBucketMinExperts experts on, the sweep and selection of the bucket route (bucket.hip);
+// 3. below, z is split into three bfloat16 pieces per element whose sum is z exactly, stored as the
+//    rows [z_hi | z_mid | z_lo] of a 3r-wide operand; when r is not a multiple of 64 the rows
+//    of R2t are stacked three times into a matching [M][3r] operand, otherwise the sweep
+//    reads each 64-wide chunk of R2t for all three pieces; the fused standard router sweeps that
+//    pair: its fp32 logits are sums of exact bf16 products, i.e. the fp32 dot products of the fp32 z
+//    with the bfloat16 expert rows up to the summation order, and it returns their exact top k
+//    (ties to the smaller id), the softmax over the k and, optionally, the selected logits.
 //
 // Exactness of the split: z = m u with |m| < 2^24 (u the fp32 unit of z's binade).  z_hi =
 // bf16(z) leaves z - z_hi = m1 u with |m1| <= 2^16, exact in fp32; z_mid = bf16(z - z_hi) leaves
@@ -38,22 +34,16 @@ constexpr int64_t kWideMaxGrid = 1 << 20;
 
 __device__ __forceinline__ uint16_t wide_bits(__bf16 v) { return __builtin_bit_cast(uint16_t, v); }
 
-// z as written by the block passes: block b holds z[t][j0 + c] at zb[T j0 + t w + c].  Columns
-// below n64 sit in 64-wide blocks, then one 32-wide block (when r mod 64 >= 32), then one
-// 16-wide block (when r mod 32 == 16).
-__global__ __launch_bounds__(kWideThreads) void wide_split_kernel(const float* __restrict__ zb,
+// zs[t] = [z_hi | z_mid | z_lo] of the fp32 row z[t].
+__global__ __launch_bounds__(kWideThreads) void wide_split_kernel(const float* __restrict__ z,
                                                                   int64_t T, int32_t r,
                                                                   uint16_t* __restrict__ zs) {
     const int64_t n = T * r;
-    const int32_t n64 = r / 64 * 64;
-    const int32_t n32 = n64 + (r % 64 >= 32 ? 32 : 0);
     for (int64_t i = (int64_t)blockIdx.x * kWideThreads + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kWideThreads) {
         const int64_t t = i / r;
         const int32_t j = (int32_t)(i - t * r);
-        const int32_t j0 = j < n64 ? (j & ~63) : (j < n32 ? n64 : n32);
-        const int32_t w = j < n64 ? 64 : (j < n32 ? 32 : 16);
-        const float v = zb[T * j0 + t * w + (j - j0)];
+        const float v = z[i];
         const __bf16 a = (__bf16)v;
         const float r1 = v - (float)a;
         const __bf16 b = (__bf16)r1;
@@ -100,46 +90,59 @@ bool wide_make_plan(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k, WideP
         k < 1 || k > M)
         return false;
     WidePlan q{};
-    int32_t j = 0;
-    size_t zscr = 0;
-    while (j < r) {
-        const int32_t left = r - j;
-        const int32_t w = left >= 64 ? 64 : (left >= 32 ? 32 : 16);
-        q.j0[q.nblocks] = j;
-        q.w[q.nblocks] = w;
-        ++q.nblocks;
-        const size_t s = zonly_workspace_bytes(T, h, w);
-        zscr = s > zscr ? s : zscr;
-        j += w;
-    }
     if (!fullrank_fused_make_plan(T, 3 * r, M, k, &q.ff)) return false;
     size_t o = 0;
     q.off_z = o;
     o += wide_align((size_t)T * r * sizeof(float));
     q.off_zscratch = o;
-    o += wide_align(zscr);
-    q.off_zs = o;
-    o += wide_align((size_t)T * 3 * r * sizeof(uint16_t));
+    o += wide_align(zpass_workspace_bytes(T, h, r));
+    q.off_zhi = o;
+    o += wide_align((size_t)T * r * sizeof(uint16_t));
+    q.off_cz = o;
+    o += wide_align((size_t)T * sizeof(float));
+    const size_t head = o;
+    // fused sweep: z_hi and the scale are not read again, the split takes their place
+    q.off_zs = q.off_zhi;
+    o = q.off_zs + wide_align((size_t)T * 3 * r * sizeof(uint16_t));  // from off_zhi on
     q.stack = r % 64 != 0;
     q.off_w3 = o;
     if (q.stack) o += wide_align((size_t)M * 3 * r * sizeof(uint16_t));
     q.off_ff = o;
     o += wide_align(q.ff.workspace_bytes);
-    q.workspace_bytes = o;
+    // what the fused sweep takes with z computed by blocks of 64, 32 and 16 columns
+    size_t zscr = 0;
+    for (int32_t j = 0; j < r;) {
+        const int32_t w = r - j >= 64 ? 64 : (r - j >= 32 ? 32 : 16);
+        const size_t s = zonly_workspace_bytes(T, h, w);
+        zscr = s > zscr ? s : zscr;
+        j += w;
+    }
+    const size_t blocks = o - wide_align(zpass_workspace_bytes(T, h, r)) + wide_align(zscr);
+    // The bucket route from kBucketMinExperts experts on: one sweep of the matrix cores instead of
+    // the three pieces' (T 16384, r 128, M 16384: 62 + 50 us against 410).  Below, its selection
+    // would read a large part of the experts' rows.  The workspace stays at least what the fused sweep
+    // took: the shapes that more_route_lowrank_noalloc takes and refuses are a contract of their own.
+    q.off_bk = head;
+    q.bucket = bucket_make_plan(T, r, M, k, head, &q.bk);
+    const size_t need = q.bucket ? head + q.bk.bytes : (o > head ? o : head);
+    q.workspace_bytes = need > blocks ? need : blocks;
     *out = q;
     return true;
 }
 
 hipError_t wide_launch(const WidePlan& p, const uint16_t* x, const uint16_t* R1t,
                        const uint16_t* R2t, int64_t T, int32_t h, int32_t r, int32_t M, int32_t k,
-                       int32_t* idx, float* gate, float* topval, void* workspace,
+                       int32_t* idx, float* gate, float* topval, int32_t* counts, void* workspace,
                        hipStream_t st) {
     char* ws = static_cast<char*>(workspace);
     float* z = reinterpret_cast<float*>(ws + p.off_z);
-    for (int32_t b = 0; b < p.nblocks; ++b) {
-        const hipError_t e = zonly_launch(x, R1t + (int64_t)p.j0[b] * h, T, h, p.w[b],
-                                          z + T * p.j0[b], ws + p.off_zscratch, st);
-        if (e != hipSuccess) return e;
+    uint16_t* zhi = reinterpret_cast<uint16_t*>(ws + p.off_zhi);
+    float* cz = reinterpret_cast<float*>(ws + p.off_cz);
+    hipError_t e = zpass_launch(x, R1t, T, h, r, z, zhi, cz, ws + p.off_zscratch, st);
+    if (e != hipSuccess) return e;
+    if (p.bucket) {
+        const BucketArgs b{z, zhi, cz, R2t, T, r, M, k, true, counts, idx, gate, topval};
+        return bucket_launch(p.bk, b, ws + p.off_bk, st);
     }
     uint16_t* zs = reinterpret_cast<uint16_t*>(ws + p.off_zs);
     uint16_t* w3 = reinterpret_cast<uint16_t*>(ws + p.off_w3);
@@ -151,7 +154,7 @@ hipError_t wide_launch(const WidePlan& p, const uint16_t* x, const uint16_t* R1t
                                               topval, ffws, st);
     hipLaunchKernelGGL(wide_stack_kernel, dim3(wide_grid((int64_t)M * 3 * (r / 8))),
                        dim3(kWideThreads), 0, st, R2t, M, r, w3);
-    const hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     return fullrank_fused_launch(p.ff, zs, w3, T, 3 * r, M, k, idx, gate, topval, ffws, st);
 }

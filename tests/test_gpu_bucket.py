@@ -71,3 +71,30 @@ def test_bucket_route_ties_take_the_exact_sweep(T):
         assert np.array_equal(a, b)
     rep = parity.evaluate(inp.x, inp.R1, inp.R2, k, idx, gate, topval)
     assert rep.ok(), str(rep)
+
+
+WIDE = [
+    # T, h, r, M, k, expert_bias_var: every rank the sweep is compiled for, padded and exact, and k > 16
+    (70, 64, 48, 2048, 4, 0.0),
+    (33, 64, 80, 2049, 9, 0.5),
+    (1100, 32, 96, 2303, 17, 0.0),
+    (300, 128, 112, 4111, 32, 0.0),
+    (1300, 64, 128, 9000, 8, 0.5),
+    (200, 48, 144, 5000, 20, 0.0),
+    (1025, 32, 192, 3000, 16, 0.0),
+    (129, 96, 240, 2600, 7, 0.25),
+    (1050, 32, 256, 2304, 32, 0.0),
+    (1030, 64, 16, 20000, 24, 0.0),
+    (90, 64, 32, 7000, 32, 0.5),
+]
+
+
+@pytest.mark.parametrize("shape", WIDE, ids=lambda s: "T%d_h%d_r%d_M%d_k%d_b%g" % s)
+def test_bucket_route_at_wide_ranks_and_long_lists(shape):
+    T, h, r, M, k, var = shape
+    assert router.lowrank_route(T, h, r, M, k) == "wide"
+    inp = make_inputs(T, h, r, M, seed=T + M, expert_bias_var=var)
+    idx, gate, topval, counts = route_lowrank(inp, k, histogram=True, tag="wide bucket")
+    rep = parity.evaluate(inp.x, inp.R1, inp.R2, k, idx, gate, topval)
+    assert rep.ok(), "%s: %s" % (shape, rep)
+    assert np.array_equal(counts, np.bincount(idx.ravel(), minlength=M).astype(np.int32))

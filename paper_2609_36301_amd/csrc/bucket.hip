@@ -359,6 +359,18 @@ struct SelectCfg {
     static constexpr int NCAND = 128;                         // candidates evaluated exactly per token
 };
 
+// (logit, expert) as an integer that orders like the selection: larger logit first, then smaller
+// expert id (-0 as +0).  Never 0 for an expert id.
+__device__ __forceinline__ uint64_t selection_key(float l, int32_t e) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, l + 0.0f);
+    const uint32_t o = u & 0x80000000u ? ~u : u | 0x80000000u;
+    return ((uint64_t)o << 32) | (uint32_t)~e;
+}
+__device__ __forceinline__ float selection_logit(uint64_t key) {
+    const uint32_t o = (uint32_t)(key >> 32);
+    return __builtin_bit_cast(float, o & 0x80000000u ? o & 0x7FFFFFFFu : ~o);
+}
+
 // Lanes of a wave (as a 64-bit mask) that keep the larger value of their pair in a bitonic stage.
 constexpr uint64_t sort_keeps_larger(int size, int d, int lpt) {
     uint64_t m = 0;
@@ -406,11 +418,11 @@ __device__ __forceinline__ float token_sort_desc(float x) {
 //     value in each lane, and the experts whose upper bound reaches theta are listed;
 //  5. those (k and a few) are evaluated exactly, a lane each, the ones with l >= theta ranked.
 // A token whose lists overflow (many ties) is swept over all M experts by the whole workgroup at
-// the end.  8 SEG NS >= r; K: list length of that sweep (>= k).
+// the end.  8 SEG NS >= r (EXACT: equal to r); K: list length of that sweep (>= k).
 // Bound by issue and by the rows' reads (r 64, M 16384: 10 buckets, 20 KB per token from L2; 32768
-// tokens in 59 us; with the rows staged in LDS and two waves' worth of registers fewer in flight
-// 92, with exact sums for all of them and a token per wave 127).
-template <int SEG, int NS, int K, bool COOP>
+// tokens in 53 us; 59 with 64-bit addresses, a reduction per row and ranks by (logit, id) pairs,
+// 92 with the rows staged in LDS, 127 with exact sums for all of them and a token per wave).
+template <int SEG, int NS, bool EXACT, int K, bool COOP>
 __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     const float* __restrict__ z, const uint16_t* __restrict__ zh, const float* __restrict__ cz,
     const uint16_t* __restrict__ R2t, const uint16_t* __restrict__ fine,
@@ -422,13 +434,13 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     constexpr int LPT = C::LPT, TPW = C::TPW, NCAND = C::NCAND, TOKENS = C::TOKENS;
     constexpr int LANES = COOP ? kSelThreads : LPT;  // lanes of a token in all
     constexpr int ZMAX = 8 * SEG * NS;        // >= r
+    constexpr uint32_t RS = 8 * SEG * NS;     // r when EXACT
     constexpr int ES = ZMAX < 64 ? ZMAX / 8 : 8;  // segments per step of the exact sum
     __shared__ __attribute__((aligned(16))) float zrow[TOKENS][ZMAX];
     __shared__ int32_t list1[TOKENS][kSelList];
     __shared__ int32_t list2[TOKENS][kSelList];
     __shared__ int32_t list3[TOKENS][NCAND];
-    __shared__ float cl[TOKENS][NCAND];
-    __shared__ int32_t ce[TOKENS][NCAND];
+    __shared__ uint64_t key[TOKENS][NCAND];   // candidates at or above theta
     __shared__ float wmax[COOP ? 2 : 1][COOP ? kSelWaves : 1][COOP ? 64 : 1];
     __shared__ int32_t found[4];              // COOP: entries of the four lists
     __shared__ float ex[TOKENS][K];
@@ -519,7 +531,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         };
         // ---- 1. and 2. coarse maxima
         constexpr int PIECE = 4 * LANES, ROUND = kSelQ * PIECE;
-        const float* crow = coarse + (int64_t)tc * nCp;
+        const float* crow = coarse + (uint32_t)tc * (uint32_t)nCp;
         const int nround = (nC + ROUND - 1) / ROUND;
         f32x4 q[kSelQ], nq[kSelQ];
         auto load_round = [&](int rd) __attribute__((always_inline)) {
@@ -574,6 +586,8 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         const int fround = (n1m + FPR * kSelFine - 1) / (FPR * kSelFine);
         float v[kSelFine], cn[kSelFine];
         int id[kSelFine];
+        const uint32_t fstride = 16u * (uint32_t)Tp;                        // of a super-group
+        const uint32_t fbase = 16u * (uint32_t)tc + (uint32_t)(sub & 7);    // token and tile
         auto load_fine = [&](int rd) __attribute__((always_inline)) {
 #pragma unroll
             for (int m = 0; m < kSelFine; ++m) {
@@ -581,9 +595,10 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
                 const int ci = list1[j][p < n1 ? p : 0];
                 id[m] = p < n1 ? ci * kSgTiles + (sub & 7) : -1;
                 const int cc = p < n1 ? ci : 0;
-                v[m] = bf16_bits_to_f32(
-                    fine[(((int64_t)(cc >> 1) * Tp + tc) * 2 + (cc & 1)) * kSgTiles + (sub & 7)]);
-                cn[m] = c * fnorm[cc * kSgTiles + (sub & 7)];
+                // (the maxima of a slab take less than 2^32 bytes)
+                const uint32_t fo = (uint32_t)(cc >> 1) * fstride + 8u * (cc & 1) + fbase;
+                v[m] = bf16_bits_to_f32(fine[fo]);
+                cn[m] = c * fnorm[(uint32_t)(cc * kSgTiles + (sub & 7))];
             }
         };
         // the fine maxima are rounded to bf16: 2^-8 relative at most (and subnormals)
@@ -670,37 +685,64 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
             const float nb = fnorm[fo];
             const bool live = rd * BPR + seg / ITB < n2 && eo < M;
             float s = 0.0f;
+            // byte offsets fit 32 bits; of a bucket's rows only the first is computed where the row
+            // stride is a constant (the others follow at constant distances)
             auto rows = [&](auto clamp) __attribute__((always_inline)) {
                 u32x4 u[SEG][NS];
 #pragma unroll
                 for (int i = 0; i < SEG; ++i) {
-                    int32_t er = eb[i / ITB] + row_of(i % ITB, grp);
-                    if constexpr (decltype(clamp)::value) er = er < M ? er : M - 1;
+                    uint32_t base;
+                    int ahead = 0;
+                    if constexpr (decltype(clamp)::value) {
+                        const int32_t er = eb[i / ITB] + row_of(i % ITB, grp);
+                        base = (uint32_t)(er < M ? er : M - 1) * (2u * (uint32_t)r);
+                    } else if constexpr (EXACT && RPT % 4 == 0) {
+                        // row_of(it, grp) = row_of(0, grp) + 2 RPT it: whole groups of four rows
+                        base = (uint32_t)(eb[i / ITB] + row_of(0, grp)) * (2u * RS);
+                        ahead = (i % ITB) * 2 * RPT * 2 * RS;
+                    } else {
+                        base = (uint32_t)(eb[i / ITB] + row_of(i % ITB, grp)) * (2u * (uint32_t)r);
+                    }
+                    const char* rowp = reinterpret_cast<const char*>(R2t) + base;
 #pragma unroll
                     for (int c = 0; c < NS; ++c) {
-                        // (segments past the rank re-read the row's first, against a zero z)
-                        const int col = 8 * (SEG * c + seg);
-                        const uint32_t off = (uint32_t)er * (uint32_t)r + (uint32_t)(col < r ? col : 0);
-                        u[i][c] = *reinterpret_cast<const u32x4*>(R2t + off);
+                        if constexpr (EXACT) {
+                            u[i][c] = *reinterpret_cast<const u32x4*>(
+                                reinterpret_cast<const char*>(R2t) + (base + 16u * seg) + ahead +
+                                16 * SEG * c);
+                        } else {
+                            // (segments past the rank re-read the row's first, against a zero z)
+                            const int col = 8 * (SEG * c + seg);
+                            u[i][c] = *reinterpret_cast<const u32x4*>(rowp + 2 * (col < r ? col : 0));
+                        }
                     }
                 }
+                float t[SEG];
 #pragma unroll
                 for (int i = 0; i < SEG; ++i) {
-                    float t = 0.0f;
+                    t[i] = 0.0f;
 #pragma unroll
                     for (int c = 0; c < NS; ++c)
 #pragma unroll
                         for (int d = 0; d < 4; ++d) {
                             const uint32_t ud = u[i][c][d], zd = zv[c][d];
-                            t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, ud),
-                                                                __builtin_bit_cast(bf16x2, zd), t,
-                                                                false);
+                            t[i] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, ud),
+                                                                   __builtin_bit_cast(bf16x2, zd),
+                                                                   t[i], false);
                         }
-                    t += lane_xor<1>(t);
-                    if constexpr (SEG >= 4) t += lane_xor<2>(t);
-                    if constexpr (SEG >= 8) t += lane_half_mirror(t);  // the quads hold their sums
-                    s = seg == i ? t : s;
                 }
+                // sums over the SEG lanes of a row, load i's ending up in lane seg = i: at each step
+                // a lane keeps one of a pair of values and adds the other lane's part of it
+                unroll<SEG == 8 ? 3 : (SEG == 4 ? 2 : 1)>([&](auto st) __attribute__((always_inline)) {
+                    constexpr int D = 1 << decltype(st)::value;
+                    const bool up = (seg & D) != 0;
+#pragma unroll
+                    for (int i = 0; i < SEG; i += 2 * D) {
+                        const float keep = up ? t[i + D] : t[i], give = up ? t[i] : t[i + D];
+                        t[i] = keep + lane_xor<D>(give);
+                    }
+                });
+                s = t[0];
             };
             if (__ballot(edge))
                 rows(std::true_type{});
@@ -746,10 +788,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
             const bool pass = i < n3 && l >= theta;
             const uint64_t mask = __ballot(pass);
             const int o = place(L3{}, mask, nc);  // at most n3 in all
-            if (pass) {
-                cl[j][o] = l;
-                ce[j][o] = e;
-            }
+            if (pass) key[j][o] = selection_key(l, e);
         }
         nc = total(L3{}, nc);
         // fewer than k cannot happen (k experts reach theta); the test is a guard, not a path
@@ -757,15 +796,16 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         nc = over ? 0 : nc;
         // rank of each candidate by counting; ranks below k write their output slot
         const int ncm = most(nc);
+        for (int i = nc + gl; i < ncm; i += LANES) key[j][i] = 0;  // (of the wave's other token: no rank)
+        if constexpr (!COOP) wave_lds_sync();
         for (int i0 = 0; i0 < ncm; i0 += LANES) {
-            const int i = i0 + gl < nc ? i0 + gl : 0;
-            const float l = cl[j][i];
-            const int32_t e = ce[j][i];
+            const uint64_t mine = key[j][i0 + gl < nc ? i0 + gl : 0];
             int rank = 0;
-            for (int t = 0; t < ncm; ++t)
-                rank += t < nc && better(cl[j][t], ce[j][t], l, e) ? 1 : 0;
+#pragma unroll 4
+            for (int t = 0; t < ncm; ++t) rank += key[j][t] > mine ? 1 : 0;
             if (ok && i0 + gl < nc && rank < k) {
-                idx[(int64_t)tok * k + rank] = e;
+                const float l = selection_logit(mine);
+                idx[(int64_t)tok * k + rank] = ~(int32_t)mine;
                 if (topval) topval[(int64_t)tok * k + rank] = l;
                 ex[j][rank] = l;
             }
@@ -902,44 +942,48 @@ void launch_sweep(const SweepGrid& g, const BucketArgs& a, int32_t T, const uint
                        Tp, nCp, fine, coarse, fnorm, cnorm, hist);
 }
 
-template <int SEG, int NS, int K, bool COOP>
+template <int SEG, int NS, bool EXACT, int K, bool COOP>
 void launch_select(const BucketArgs& a, int64_t t0, int32_t T, int32_t Tp, int32_t nCp,
                    const uint32_t* fine, const float* coarse, const float* fnorm, const float* cnorm,
                    hipStream_t st) {
     constexpr int TOK = SelectCfg<K, COOP>::TOKENS;
-    hipLaunchKernelGGL((bucket_select_kernel<SEG, NS, K, COOP>), dim3((unsigned)((T + TOK - 1) / TOK)),
+    hipLaunchKernelGGL((bucket_select_kernel<SEG, NS, EXACT, K, COOP>), dim3((unsigned)((T + TOK - 1) / TOK)),
                        dim3(kSelThreads), 0, st, a.z + t0 * a.r, a.zhi + t0 * a.r, a.cz + t0,
                        a.R2t, reinterpret_cast<const uint16_t*>(fine), coarse, fnorm, cnorm, T, Tp,
                        nCp, a.r, a.M, a.k, a.pieces, a.idx + t0 * a.k, a.gate + t0 * a.k,
                        a.topval ? a.topval + t0 * a.k : nullptr);
 }
 
-template <int SEG, int NS>
+template <int SEG, int NS, bool EXACT>
 void launch_select_k(const BucketArgs& a, int64_t t0, int32_t T, int32_t Tp, int32_t nCp,
                      const uint32_t* fine, const float* coarse, const float* fnorm,
                      const float* cnorm, hipStream_t st) {
-    constexpr int SEG4 = SEG < 4 ? 4 : SEG;  // 64 lanes per token: at most 16 rows per load
+    constexpr int S4 = SEG < 4 ? 4 : SEG;  // 64 lanes per token: at most 16 rows per load
+    constexpr bool X4 = EXACT && SEG >= 4;
+#define MORE_SELECT(S, X, K, COOP) \
+    launch_select<S, NS, X, K, COOP>(a, t0, T, Tp, nCp, fine, coarse, fnorm, cnorm, st)
     if (T <= kSelCoopTokens) {
         if (a.k <= 8)
-            launch_select<SEG4, NS, 8, true>(a, t0, T, Tp, nCp, fine, coarse, fnorm, cnorm, st);
+            MORE_SELECT(S4, X4, 8, true);
         else if (a.k <= 16)
-            launch_select<SEG4, NS, 16, true>(a, t0, T, Tp, nCp, fine, coarse, fnorm, cnorm, st);
+            MORE_SELECT(S4, X4, 16, true);
         else
-            launch_select<SEG4, NS, 32, true>(a, t0, T, Tp, nCp, fine, coarse, fnorm, cnorm, st);
+            MORE_SELECT(S4, X4, 32, true);
     } else if (a.k <= 8) {
-        launch_select<SEG, NS, 8, false>(a, t0, T, Tp, nCp, fine, coarse, fnorm, cnorm, st);
+        MORE_SELECT(SEG, EXACT, 8, false);
     } else if (a.k <= 16) {
-        launch_select<SEG, NS, 16, false>(a, t0, T, Tp, nCp, fine, coarse, fnorm, cnorm, st);
+        MORE_SELECT(SEG, EXACT, 16, false);
     } else {
-        launch_select<SEG4, NS, 32, false>(a, t0, T, Tp, nCp, fine, coarse, fnorm, cnorm, st);
+        MORE_SELECT(S4, X4, 32, false);
     }
+#undef MORE_SELECT
 }
 
 }  // namespace
 
 bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t z_bytes, BucketPlan* p) {
     if (M < kBucketMinExperts || M > kBucketMaxExperts || r < 16 || r % 16 != 0 ||
-        r > kBucketMaxRank || k > 32 || T < 1 || (int64_t)M * r >= ((int64_t)1 << 32))
+        r > kBucketMaxRank || k > 32 || T < 1 || (int64_t)M * r >= ((int64_t)1 << 31))
         return false;
     const int32_t nsg = (M + kSgExperts - 1) / kSgExperts;
     size_t room = kScratchAim > z_bytes ? kScratchAim - z_bytes : 0;
@@ -992,18 +1036,22 @@ hipError_t bucket_launch(const BucketPlan& p, const BucketArgs& a, void* scratch
             case 16: launch_sweep<16>(g, a, T, zh, Tp, p.nCp, fine, coarse, fnorm, cnorm, hist, st); break;
             default: return hipErrorInvalidValue;
         }
-        switch (a.r <= 32 ? 0 : (a.r + 63) / 64) {
-            case 0:
-                if (a.r <= 16)
-                    launch_select_k<2, 1>(a, t0, T, Tp, p.nCp, fine, coarse, fnorm, cnorm, st);
+#define MORE_SELECT_R(SEG, NS, EXACT) \
+    launch_select_k<SEG, NS, EXACT>(a, t0, T, Tp, p.nCp, fine, coarse, fnorm, cnorm, st)
+        switch (a.r) {
+            case 16: MORE_SELECT_R(2, 1, true); break;
+            case 32: MORE_SELECT_R(4, 1, true); break;
+            case 64: MORE_SELECT_R(8, 1, true); break;
+            case 128: MORE_SELECT_R(8, 2, true); break;
+            default:
+                if (a.r < 64)
+                    MORE_SELECT_R(8, 1, false);
+                else if (a.r < 128)
+                    MORE_SELECT_R(8, 2, false);
                 else
-                    launch_select_k<4, 1>(a, t0, T, Tp, p.nCp, fine, coarse, fnorm, cnorm, st);
-                break;
-            case 1: launch_select_k<8, 1>(a, t0, T, Tp, p.nCp, fine, coarse, fnorm, cnorm, st); break;
-            case 2: launch_select_k<8, 2>(a, t0, T, Tp, p.nCp, fine, coarse, fnorm, cnorm, st); break;
-            case 3: launch_select_k<8, 3>(a, t0, T, Tp, p.nCp, fine, coarse, fnorm, cnorm, st); break;
-            default: launch_select_k<8, 4>(a, t0, T, Tp, p.nCp, fine, coarse, fnorm, cnorm, st); break;
+                    MORE_SELECT_R(8, 4, false);
         }
+#undef MORE_SELECT_R
     }
     return hipGetLastError();
 }

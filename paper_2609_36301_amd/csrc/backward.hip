@@ -84,17 +84,42 @@ __device__ __forceinline__ bf16x8 lds_two_quads(const uint16_t* p0, const uint16
 // ------------------------------------------------------------------------------ prep
 // One thread per element of z [T][r]: zhl [T][2r] = bf16(z'), bf16(z' - bf16(z')) with
 // z' = z log2(e); zb [T][r] = bf16(z); bias[t] = -(m log2(e) + log2 Z) (when m is given).
-__global__ __launch_bounds__(256) void bwd_prep_kernel(const float* __restrict__ z,
-                                                       const float* __restrict__ m,
-                                                       const float* __restrict__ Z, int32_t T,
-                                                       int32_t r, uint16_t* __restrict__ zhl,
-                                                       uint16_t* __restrict__ zb,
-                                                       float* __restrict__ bias) {
+// Blocks [0, zblocks) take the elements of z; with splits > 1 they also add the z pass's partials (in
+// split order) and write z.  The other blocks write R1 [h][r] from R1t [r][h].  (One launch instead of
+// three: each costs about 4.5 us on the smallest shapes.)
+__global__ __launch_bounds__(256) void bwd_prep_kernel(
+    const float* __restrict__ zparts, int32_t splits, const float* __restrict__ m,
+    const float* __restrict__ Z, int32_t T, int32_t r, float* __restrict__ z,
+    uint16_t* __restrict__ zhl, uint16_t* __restrict__ zb, float* __restrict__ bias,
+    const uint16_t* __restrict__ R1t, int32_t h, uint16_t* __restrict__ R1, int64_t zblocks) {
+    if (blockIdx.x >= zblocks) {  // workgroup-uniform
+        const int64_t i = ((int64_t)blockIdx.x - zblocks) * 256 + threadIdx.x;  // index into R1
+        if (i >= (int64_t)h * r) return;
+        const int64_t c = i / r;
+        const int32_t j = (int32_t)(i - c * r);
+        R1[i] = R1t[(int64_t)j * h + c];
+        return;
+    }
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)T * r) return;
+    const int64_t n = (int64_t)T * r;
+    if (i >= n) return;
     const int64_t t = i / r;
     const int32_t j = (int32_t)(i - t * r);
-    const float zv = z[i];
+    float zv = 0.0f;
+    if (splits > 1) {  // (zparts and z are different arrays)
+        int p = 0;
+        for (; p + 16 <= splits; p += 16) {  // 16 loaded before they are added, in order
+            float v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = zparts[(int64_t)(p + q) * n + i];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) zv += v[q];
+        }
+        for (; p < splits; ++p) zv += zparts[(int64_t)p * n + i];
+        z[i] = zv;
+    } else {
+        zv = zparts[i];
+    }
     const float v = zv * kBwLog2e;
     const __bf16 hb = (__bf16)v;
     const __bf16 lb = (__bf16)(v - (float)hb);
@@ -102,17 +127,6 @@ __global__ __launch_bounds__(256) void bwd_prep_kernel(const float* __restrict__
     zhl[t * 2 * r + r + j] = __builtin_bit_cast(uint16_t, lb);
     zb[i] = __builtin_bit_cast(uint16_t, (__bf16)zv);
     if (m && j == 0) bias[t] = -(m[t] * kBwLog2e + log2f(Z[t]));
-}
-
-// R1 [h][r] from R1t [r][h].
-__global__ __launch_bounds__(256) void bwd_r1_transpose_kernel(const uint16_t* __restrict__ R1t,
-                                                               int32_t h, int32_t r,
-                                                               uint16_t* __restrict__ R1) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // index into R1
-    if (i >= (int64_t)h * r) return;
-    const int64_t c = i / r;
-    const int32_t j = (int32_t)(i - c * r);
-    R1[i] = R1t[(int64_t)j * h + c];
 }
 
 // ------------------------------------------------------------------------------ token-major
@@ -696,10 +710,11 @@ __global__ __launch_bounds__(256) void bwd_sparse_kernel(const int32_t* __restri
     const int64_t q0 = c * kBwChunk;
     const int cnt = (int)min((int64_t)kBwChunk, nv - q0);
     if (cnt <= 0) return;  // wave-uniform
-    int32_t pl = 0, el = 0, o0l = 0, o1l = 1;
+    int32_t tl = 0, el = 0, o0l = 0, o1l = 1;  // token, expert and the expert's range
     float vl = 0.0f;
     if (lane < cnt) {
-        pl = sorted[q0 + lane];
+        const int32_t pl = sorted[q0 + lane];
+        tl = pl / k;  // (divided here, a lane per entry: one by one below it took half the time)
         el = idx[pl];
         vl = dtop[pl];
         o0l = offsets[el];  // the entry's expert range, loaded for all entries at once
@@ -708,9 +723,9 @@ __global__ __launch_bounds__(256) void bwd_sparse_kernel(const int32_t* __restri
     // run ending at entry u (its expert's range read from lane u; dense: its dR2 row's value when
     // accumulating)
     auto flush = [&](int32_t e, int u, float acc, float dense) __attribute__((always_inline)) {
-        const int64_t o0 = __builtin_amdgcn_readlane(o0l, u);
-        const int64_t o1 = __builtin_amdgcn_readlane(o1l, u);
-        const int64_t c0 = o0 / kBwChunk, c1 = (o1 - 1) / kBwChunk;
+        const int32_t o0 = __builtin_amdgcn_readlane(o0l, u);
+        const int32_t o1 = __builtin_amdgcn_readlane(o1l, u);
+        const int32_t c0 = o0 / kBwChunk, c1 = (o1 - 1) / kBwChunk;
         if (lane < r) {
             if (c0 == c1)
                 dR2t[(int64_t)e * r + lane] = accumulate ? dense + acc : acc;
@@ -726,8 +741,8 @@ __global__ __launch_bounds__(256) void bwd_sparse_kernel(const int32_t* __restri
     float zv[kBwChunk];
 #pragma unroll
     for (int u = 0; u < kBwChunk; ++u) {
-        const int32_t p = __builtin_amdgcn_readlane(pl, u);  // 0 past cnt: a valid row
-        zv[u] = lane < r ? z[(int64_t)(p / k) * r + lane] : 0.0f;
+        const int32_t t = __builtin_amdgcn_readlane(tl, u);  // 0 past cnt: a valid row
+        zv[u] = lane < r ? z[(int64_t)t * r + lane] : 0.0f;
     }
     // accumulating: the dense dR2 rows of the entries' experts, also all in flight at once
     float dv[kBwChunk];
@@ -1153,17 +1168,19 @@ hipError_t backward_launch(const BackwardPlan& p, const BackwardArgs& a, void* w
         return hipGetLastError();
     }
     float* z = reinterpret_cast<float*>(ws + p.off_z);
-    hipError_t e = zonly_launch(a.x, a.R1t, a.T, a.h, r, z, ws + p.off_zscratch, st);
+    const float* zparts = nullptr;
+    int32_t zsplits = 1;
+    hipError_t e = zparts_launch(a.x, a.R1t, a.T, a.h, r, z, ws + p.off_zscratch, &zparts, &zsplits,
+                                 st);
     if (e != hipSuccess) return e;
-    const int64_t nz = (int64_t)a.T * r;
-    hipLaunchKernelGGL(bwd_prep_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, z,
-                       p.balance ? a.m : nullptr, a.Z, a.T, r,
+    const int64_t zblocks = ((int64_t)a.T * r + 255) / 256;
+    const int64_t rblocks = ((int64_t)a.h * r + 255) / 256;
+    hipLaunchKernelGGL(bwd_prep_kernel, dim3((unsigned)(zblocks + rblocks)), dim3(256), 0, st,
+                       zparts, zsplits, p.balance ? a.m : nullptr, a.Z, a.T, r, z,
                        reinterpret_cast<uint16_t*>(ws + p.off_zhl),
                        reinterpret_cast<uint16_t*>(ws + p.off_zb),
-                       reinterpret_cast<float*>(ws + p.off_bias));
-    const int64_t nr1 = (int64_t)a.h * r;
-    hipLaunchKernelGGL(bwd_r1_transpose_kernel, dim3((unsigned)((nr1 + 255) / 256)), dim3(256), 0,
-                       st, a.R1t, a.h, r, reinterpret_cast<uint16_t*>(ws + p.off_r1));
+                       reinterpret_cast<float*>(ws + p.off_bias), a.R1t, a.h,
+                       reinterpret_cast<uint16_t*>(ws + p.off_r1), zblocks);
     if (p.balance) {
         switch (p.RC) {
             case 1: launch_balance<1>(p, a, ws, st); break;

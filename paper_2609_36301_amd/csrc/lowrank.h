@@ -68,7 +68,13 @@ size_t zpass_workspace_bytes(int64_t T, int32_t h, int32_t r);
 hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
                         float* z, uint16_t* zhi, float* cz, void* scratch, hipStream_t stream);
 
-// z alone (z_hi and the scale go to the scratch as well).
+// The z pass without the sum over its h splits, for a caller whose next kernel takes it: returns the
+// partials in *parts, [*splits][T][r], to be added in order (one split: *parts == z).
+hipError_t zparts_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
+                         float* z, void* scratch, const float** parts, int32_t* splits,
+                         hipStream_t stream);
+
+// z alone (z_hi and the scale go to the scratch as well; zparts_launch takes the same scratch).
 size_t zonly_workspace_bytes(int64_t T, int32_t h, int32_t r);
 hipError_t zonly_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
                         float* z, void* scratch, hipStream_t stream);

@@ -1342,11 +1342,10 @@ size_t zpass_workspace_bytes(int64_t T, int32_t h, int32_t r) {
     return hs > 1 ? align256((size_t)hs * T * r * sizeof(float)) : 0;
 }
 
-hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
-                        float* z, uint16_t* zhi, float* cz, void* scratch, hipStream_t st) {
-    int32_t sps, hs;
-    zpass_split(T, h, &sps, &hs);
-    float* zparts = hs > 1 ? static_cast<float*>(scratch) : z;
+// The z pass alone, into zparts (z itself with one split).
+static void zpass_only(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
+                       float* zparts, uint16_t* zhi, float* cz, int32_t sps, int32_t hs,
+                       hipStream_t st) {
     const int64_t zblocks = (T + kZTokens - 1) / kZTokens;
     const dim3 grid((unsigned)(zblocks * hs));  // no group-norm workgroups
     constexpr int D = 2;
@@ -1363,6 +1362,14 @@ hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32
     else
         MORE_ZPASS(8);
 #undef MORE_ZPASS
+}
+
+hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
+                        float* z, uint16_t* zhi, float* cz, void* scratch, hipStream_t st) {
+    int32_t sps, hs;
+    zpass_split(T, h, &sps, &hs);
+    float* zparts = hs > 1 ? static_cast<float*>(scratch) : z;
+    zpass_only(x, R1t, T, h, r, zparts, zhi, cz, sps, hs, st);
     if (hs > 1) launch_zreduce(zparts, z, zhi, cz, T, r, hs, st);
     return hipGetLastError();
 }
@@ -1370,6 +1377,22 @@ hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32
 size_t zonly_workspace_bytes(int64_t T, int32_t h, int32_t r) {
     return zpass_workspace_bytes(T, h, r) + align256((size_t)T * r * sizeof(uint16_t)) +
            align256((size_t)T * sizeof(float));
+}
+
+hipError_t zparts_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
+                         float* z, void* scratch, const float** parts, int32_t* splits,
+                         hipStream_t st) {
+    int32_t sps, hs;
+    zpass_split(T, h, &sps, &hs);
+    char* s = static_cast<char*>(scratch);
+    const size_t o1 = zpass_workspace_bytes(T, h, r);
+    const size_t o2 = o1 + align256((size_t)T * r * sizeof(uint16_t));
+    float* zparts = hs > 1 ? reinterpret_cast<float*>(s) : z;
+    zpass_only(x, R1t, T, h, r, zparts, reinterpret_cast<uint16_t*>(s + o1),
+               reinterpret_cast<float*>(s + o2), sps, hs, st);
+    *parts = zparts;
+    *splits = hs;
+    return hipGetLastError();
 }
 
 hipError_t zonly_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,

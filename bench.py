@@ -45,19 +45,17 @@ def algorithmic(w):
     return nbytes, flops
 
 
-SCOPE_RESIDENT = ("one routing call: the z pass, screen, threshold, collect and finalize "
-                  "kernels (+ histogram), timed together as one step")
+SCOPE_BUCKET = ("one routing call: the z pass, the expert sweep that keeps bucket maxima and the "
+                "selection (+ histogram), timed together as one step")
 SCOPE_FUSED = ("one routing call: the z pass and the fused route kernel (screen, threshold, "
                "collect and finalize in one launch) (+ histogram), timed together as one step")
 SCOPE_LOCAL = ("one routing call: one launch of the local fused kernel (z pass, wave norm "
                "bounds, screen, threshold, collect and finalize) (+ histogram)")
-SCOPE_SINGLE = ("one routing call: the z + prescreen, collect and finalize kernels and the "
-                "histogram kernel, timed together as one step")
-SCOPE_WIDE = ("one routing call: the z pass per rank block, the three-piece split of z, the "
-              "stacked expert rows and the fused 3r-wide sweep (+ histogram), timed together as "
-              "one step")
-SCOPES = {"expert-resident": SCOPE_RESIDENT, "fused": SCOPE_FUSED, "fused-local": SCOPE_LOCAL,
-          "single-pass": SCOPE_SINGLE, "wide": SCOPE_WIDE}
+SCOPE_WIDE = ("one routing call: the z pass over all rank columns, then the expert sweep and the "
+              "selection (fewer than 2048 experts: the three-piece split of z and the fused "
+              "3r-wide sweep) (+ histogram), timed together as one step")
+SCOPES = {"expert-resident": SCOPE_BUCKET, "fused": SCOPE_FUSED, "fused-local": SCOPE_LOCAL,
+          "single-pass": SCOPE_BUCKET, "wide": SCOPE_WIDE}
 
 
 KERNEL_SOURCES = ("lowrank.hip", "lowrank.h", "device_common.h", "route_device.h",

@@ -10,7 +10,7 @@
 // Kernels of one call (the balancing kernels run only when pbar is given):
 //   zonly            z = x R1 (fp32, the z pass of the routing call)
 //   bwd_prep         z' = z log2(e) as bf16 hi/lo rows, bf16(z) rows and the token bias
-//                    -(m log2(e) + log2 Z); bwd_r1_transpose: R1 as [h][r]
+//                    -(m log2(e) + log2 Z), and R1 as [h][r]
 //   bwd_tok<false>   sweep 1, token-major: per (expert split, token) sum_e pbar_e P_te
 //   bwd_colsum       g = the split sums in split order
 //   bwd_tok<true>    sweep 2, token-major: ybar tile by tile, dz partials per expert split,

@@ -196,12 +196,6 @@ __device__ __forceinline__ void lane_pair16(float x, float& a, float& b) {
     b = __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
-// The value of x in lane 7 - l of the 8-lane group (for sums already equal within each quad).
-__device__ __forceinline__ float lane_half_mirror(float x) {
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x141, 0xF, 0xF, false));
-}
-
 // x plus its value in lane l ^ 32.
 __device__ __forceinline__ float sum_pair32(float x) {
     float a, b;

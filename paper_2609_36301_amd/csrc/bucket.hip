@@ -463,11 +463,15 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         const int32_t tc = ok ? tok : T - 1;  // a wave's second token may lie past T
         const float c = cz[tc];
         float zn = 0.0f;                      // ||z||, for the rounding of the bf16 dot products
+        uint32_t bits = 0;
         for (int i = 4 * sub; i < r; i += 4 * LPT) {
             const f32x4 v = *reinterpret_cast<const f32x4*>(z + (int64_t)tc * r + i);
             if (!COOP || w == 0) *reinterpret_cast<f32x4*>(&zrow[j][i]) = v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) zn = fmaf(v[e], v[e], zn);
+            for (int e = 0; e < 4; ++e) {
+                zn = fmaf(v[e], v[e], zn);
+                bits |= __builtin_bit_cast(uint32_t, v[e]) << 1;  // 0 for +-0 alone
+            }
         }
         // lanes of the token set in mask: those below this lane, and all
         auto below = [&](uint64_t mask) __attribute__((always_inline)) {
@@ -481,6 +485,10 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
             if constexpr (LPT == 64) return (int)__popcll(mask);
             return __builtin_popcount(tk ? (uint32_t)(mask >> 32) : (uint32_t)mask);
         };
+        // z = 0 (a padding token): every logit is 0 and the smallest ids win.  Nothing is listed for
+        // it; through the lists it would be a tie of all experts, and the sweep at the end.
+    XX
+        const bool zero = all(__ballot(bits != 0)) == 0;
         // LDS written by the token's lanes is read by them
         auto sync = [&]() __attribute__((always_inline)) {
             if constexpr (COOP)
@@ -565,6 +573,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
             });
         }
         float theta = kth(L0{}, lm);
+        theta = zero ? __builtin_inff() : theta;
         int n1 = 0;
         for (int rd = 0; rd < nround; ++rd) {
             if (nround > 1) load_round(rd);
@@ -792,7 +801,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         }
         nc = total(L3{}, nc);
         // fewer than k cannot happen (k experts reach theta); the test is a guard, not a path
-        over = over || nc < k;
+        over = (over || nc < k) && !zero;
         nc = over ? 0 : nc;
         // rank of each candidate by counting; ranks below k write their output slot
         const int ncm = most(nc);
@@ -809,6 +818,11 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
                 if (topval) topval[(int64_t)tok * k + rank] = l;
                 ex[j][rank] = l;
             }
+        }
+        if (ok && zero && gl < k) {
+            idx[(int64_t)tok * k + gl] = gl;
+            if (topval) topval[(int64_t)tok * k + gl] = 0.0f;
+            ex[j][gl] = 0.0f;
         }
         sync();
         const float mine = expf(ex[j][gl < k ? gl : 0] - ex[j][0]);

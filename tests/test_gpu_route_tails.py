@@ -1,6 +1,7 @@
-"""Inputs that make the bucket route's lists long must not stall a call: padding tokens.  Times are
-compared with the same shape on plain inputs; the bounds are several times what is measured and
-a fraction of what sweeping all experts for such tokens takes."""
+"""Inputs that make the bucket route's lists long: padding tokens and experts that tie.
+Results stay exact, and a call does not stall: times are compared with the same shape on plain
+inputs, with bounds several times what is measured and a fraction of what sweeping all experts for
+such tokens takes."""
 import numpy as np
 import pytest
 
@@ -10,6 +11,10 @@ from paper_2609_36301_amd import router
 from paper_2609_36301_amd.inputs import make_inputs, transposed_factors
 
 pytestmark = pytest.mark.gpu
+
+
+def _f64(bits):
+    return (bits.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
 
 
 def _us(inp, k):
@@ -38,3 +43,39 @@ def test_padding_tokens_cost_no_more_than_others(T, h, r, M, k):
     assert np.all(topval[zero] == 0.0)
     rep = parity.evaluate(inp.x, inp.R1, inp.R2, k, idx, gate, topval)
     assert rep.ok(), str(rep)
+
+
+# every form of the selection: rank (padded and exact), list length, one token per workgroup and packed
+TIES = [(T, r, M, k) for T in (37, 1041) for r, M, k in (
+    (16, 16500, 8), (16, 16500, 16), (32, 9000, 3), (64, 6000, 16), (48, 2048, 8), (80, 2300, 9), (128, 2049, 8),
+    (128, 4100, 32), (112, 4111, 17), (256, 2100, 32), (240, 5000, 16), (32, 2600, 24))]
+
+
+@pytest.mark.parametrize("shape", TIES, ids=lambda s: "T%d_r%d_M%d_k%d" % s)
+def test_tying_experts(shape):
+    """All experts are copies of six: each token ties M / 6 or so of them at its largest logit, and the
+    smallest ids win.  Then all experts are equal, and all zero."""
+    T, r, M, k = shape
+    h = 64
+    inp = make_inputs(T, h, r, M, seed=T + M + r)
+    which = np.random.default_rng(M).integers(0, 6, M)
+    inp.R2[:] = inp.R2[:, which]
+    idx, gate, topval, counts = route_lowrank(inp, k, histogram=True, tag="copies of six")
+    z = _f64(inp.x) @ _f64(inp.R1)
+    logits = z @ _f64(inp.R2[:, [int(np.nonzero(which == i)[0][0]) for i in range(6)]])
+    top2 = np.sort(logits, axis=1)[:, -2:]
+    clear = top2[:, 1] - top2[:, 0] > 1e-4
+    assert clear.mean() > 0.9
+    first = np.stack([np.nonzero(which == i)[0][:k] for i in range(6)]).astype(np.int32)
+    assert np.array_equal(idx[clear], first[logits.argmax(axis=1)][clear])
+    assert np.allclose(gate, 1.0 / k, atol=1e-6)
+    assert np.allclose(topval[clear], top2[clear, 1:], rtol=1e-4, atol=1e-4)
+    assert np.array_equal(counts, np.bincount(idx.ravel(), minlength=M))
+    if r in (16, 32, 64) and k <= 16:
+        for a, b in zip((idx, gate, topval), route_lowrank(inp, k, m_chunks=8, tag="resident kernels")):
+            assert np.array_equal(a, b)
+    for value in (inp.R2[:, :1].copy(), 0):
+        inp.R2[:] = value
+        idx, gate, _, _ = route_lowrank(inp, k, tag="equal experts")
+        assert np.array_equal(idx, np.broadcast_to(np.arange(k, dtype=np.int32), (T, k)))
+        assert np.allclose(gate, 1.0 / k, atol=1e-6)

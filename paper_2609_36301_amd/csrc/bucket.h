@@ -15,13 +15,15 @@ constexpr int32_t kBucketMaxExperts = 1 << 24;
 struct BucketPlan {
     int64_t slab;  // tokens per sweep and select launch
     int32_t nCp;   // floats per token of the coarse maxima
+    size_t off_cd;  // d of the screening bounds, all tokens (the z pass writes it)
     size_t off_fine, off_coarse, off_fnorm, off_cnorm, bytes;
 };
 
 struct BucketArgs {
     const float* z;        // fp32 [T][r]
     const uint16_t* zhi;   // bf16(z) [T][r]
-    const float* cz;       // screening scale [T]
+    const float* cz;       // screening scales c and d [T] (screen_scale, mean_scale)
+    const float* cd;
     const uint16_t* R2t;
     int64_t T;
     int32_t r, M, k;

@@ -12,11 +12,16 @@
 //                         experts of the few fine buckets that still can are evaluated exactly in
 //                         fp32 and ranked.
 //
-// Screening bounds.  With the token's scale c (route_device.h) and N >= ||u_e|| for the 256
-// experts of a super-group, s_e - c N <= l_e <= s_e + c N.  A bucket's maximum belongs to one of its
-// experts, so the k largest of (maximum - c N) over distinct buckets are reached by k distinct
+// Screening bounds.  With the token's scales c and d (route_device.h) and, over a bucket's experts,
+// N >= ||u'|| and m >= |mu| of the rows u = mu 1 + u' (mu the row's mean), the logit lies within
+// w = c N + d m of s_e.  (A per-expert offset, as a skewed load has, puts most of a long row's norm
+// into mu, where only the sum of z's rounding errors meets it: with offsets of variance 0.5 at r 256,
+// M 65536, k 8 a token has 10 fine buckets to read instead of 70, and 21 instead of 770 at most; 4096
+// tokens 195 us a call instead of 980.  The selection at T 16384, r 64, M 65536: 71 us before, 40.)
+// A bucket's maximum belongs to one of its
+// experts, so the k largest of (maximum - w) over distinct buckets are reached by k distinct
 // experts, and theta, the k-th of them, is a lower bound of the k-th logit.  An expert of the top k
-// has l_e >= theta, so its bucket's maximum is at least theta - c N: no other bucket is read.  The
+// has l_e >= theta, so its bucket's maximum is at least theta - w: no other bucket is read.  The
 // candidates' logits are evaluated as on the other routes (fp32 z times the bf16 row, rank entries in
 // increasing order), and l >= theta keeps k or more of them, so the result is the exact top k
 // under the total order (larger logit first, then smaller expert id) of the fp32 logits.
@@ -70,6 +75,15 @@ struct SweepCfg {
     }
 };
 
+// N and m of one row from its fp32 sums of squares and of entries, both by chains of up to 128 bf16
+// dot products rounding by 2^-22 each: 2^-13 of the square covers them (and any mu near the mean will do).
+__device__ __forceinline__ float2 row_bounds(float ss, float su, float rinv) {
+    const float mu = su * rinv;
+    return make_float2(sqrtf(fmaf(ss, 0x1p-13f, fmaxf(fmaf(-su, mu, ss), 0.0f))) * (1.0f + 0x1p-20f),
+                       fabsf(mu) * (1.0f + 0x1p-20f));
+}
+constexpr uint32_t kOnes = 0x3F803F80u;  // two bf16 ones
+
 __device__ __forceinline__ float max16(const f32x16& a) {
     float m = fmaxf(fmaxf(a[0], a[1]), a[2]);
 #pragma unroll
@@ -90,12 +104,12 @@ template <int RC>
 __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
     const uint16_t* __restrict__ zh, const uint16_t* __restrict__ R2t, int32_t T, int32_t r,
     int32_t M, int32_t chunks, int32_t splits, int32_t ew, int32_t Tp, int32_t nCp,
-    uint32_t* __restrict__ fine, float* __restrict__ coarse, float* __restrict__ fnorm,
-    float* __restrict__ cnorm, int32_t* __restrict__ hist) {
+    uint32_t* __restrict__ fine, float* __restrict__ coarse, float2* __restrict__ fnorm,
+    float2* __restrict__ cnorm, int32_t* __restrict__ hist) {
     using C = SweepCfg<RC>;
     constexpr int TPW = C::TPW, H = C::HALVES ? TPW / 2 : TPW;
     __shared__ __attribute__((aligned(16))) uint16_t rows[C::SGS * kSgExperts * C::STRIDE];
-    __shared__ float nred[16];
+    __shared__ float2 nred[16];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -299,13 +313,12 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
         }
     }
 
-    // ---- norm bounds of the buckets; the splits share the chunk's super-groups.  (The bf16 dot
-    // products round by 2^-18 relative at most, which the 2^-20 here and the 2^-10 of the screening
-    // scale cover.)
+    // ---- norm bounds of the buckets; the splits share the chunk's super-groups.
+    const float rinv = 1.0f / (float)r;
     for (int i = split; i < nl; i += splits) {      // workgroup-uniform
         if (tid < kSgExperts) {
             const int e = i * kSgExperts + tid;
-            float ss = 0.0f;
+            float ss = 0.0f, su = 0.0f;
 #pragma unroll
             for (int sg = 0; sg < C::SPR; ++sg) {
                 const bf16x8 v = load_bf16x8(rows + e * C::STRIDE + C::pos(e, sg) * 8);
@@ -313,14 +326,19 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
                 for (int q = 0; q < 8; q += 2) {
                     const bf16x2 pq = {v[q], v[q + 1]};
                     ss = __builtin_amdgcn_fdot2_f32_bf16(pq, pq, ss, false);
+                    su = __builtin_amdgcn_fdot2_f32_bf16(pq, __builtin_bit_cast(bf16x2, kOnes), su, false);
                 }
             }
+            float2 nb = row_bounds(ss, su, rinv);
             // the 16 rows of a tile in the same lane half
-            ss = fmaxf(ss, lane_xor<1>(ss));
-            ss = fmaxf(ss, lane_xor<2>(ss));
-            ss = fmaxf(ss, lane_xor<8>(ss));
-            ss = fmaxf(ss, lane_xor<16>(ss));
-            const float nb = sqrtf(ss) * (1.0f + 0x1p-20f);
+            auto over = [&](auto d) __attribute__((always_inline)) {
+                nb.x = fmaxf(nb.x, lane_xor<decltype(d)::value>(nb.x));
+                nb.y = fmaxf(nb.y, lane_xor<decltype(d)::value>(nb.y));
+            };
+            over(std::integral_constant<int, 1>{});
+            over(std::integral_constant<int, 2>{});
+            over(std::integral_constant<int, 8>{});
+            over(std::integral_constant<int, 16>{});
             if ((lane & 27) == 0) {
                 const int f = ((tid >> 2) & 1) * kSgTiles + (tid >> 5);
                 fnorm[(s0 + i) * 16 + f] = nb;
@@ -329,9 +347,12 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
         }
         __syncthreads();
         if (tid < 2) {
-            float m = nred[tid * kSgTiles];
+            float2 m = nred[tid * kSgTiles];
 #pragma unroll
-            for (int q = 1; q < kSgTiles; ++q) m = fmaxf(m, nred[tid * kSgTiles + q]);
+            for (int q = 1; q < kSgTiles; ++q) {
+                m.x = fmaxf(m.x, nred[tid * kSgTiles + q].x);
+                m.y = fmaxf(m.y, nred[tid * kSgTiles + q].y);
+            }
             cnorm[2 * (s0 + i) + tid] = m;
         }
         __syncthreads();
@@ -359,7 +380,9 @@ struct SelectCfg {
     static constexpr int NCAND = 128;                         // candidates evaluated exactly per token
 };
 
-// Of a token whose lists are long (the end of bucket_select_kernel).
+// Of a token whose lists are long (the end of bucket_select_kernel); in the place of the lists of the
+// tokens side by side, whose 32000 bytes at r 64 let five workgroups share a CU (another 1 KB, four of
+// them: 60.2 us instead of 56.6 at T 32768, M 16384).
 constexpr int kLongBuckets = 32;  // fine buckets per batch
 template <int K>
 struct LongLists {
@@ -369,6 +392,7 @@ struct LongLists {
     float bound[kSelThreads];
     int32_t cand[16 * kLongBuckets];           // experts of a batch and their upper bounds
     float cbound[16 * kLongBuckets];
+    float wmax[kSelWaves][64];                 // lower bounds by wave and lane
 };
 
 // (logit, expert) as an integer that orders like the selection: larger logit first, then smaller
@@ -420,6 +444,269 @@ __device__ __forceinline__ float token_sort_desc(float x) {
     return x;
 }
 
+// The fine maxima are rounded to bf16: 2^-8 relative at most (and subnormals).
+__device__ __forceinline__ float slack(float x) { return fmaf(fabsf(x), 0x1.01p-8f, 0x1p-125f); }
+
+// The logit of the expert with row ur for the token with row zr (LDS): rank entries in increasing
+// order (pieces: sums of eight, added up); ES segments of eight per step.
+template <int ES>
+__device__ __forceinline__ float exact_logit(const uint16_t* __restrict__ ur, const float* zr, int32_t r,
+                                             bool pieces) {
+    float l = 0.0f;
+    for (int c0 = 0; c0 < r; c0 += 8 * ES) {
+        const int ns = r - c0 < 8 * ES ? (r - c0) / 8 : ES;
+        bf16x8 u[ES];
+#pragma unroll
+        for (int g = 0; g < ES; ++g) u[g] = load_bf16x8(ur + c0 + 8 * (g < ns ? g : 0));
+#pragma unroll
+        for (int g = 0; g < ES; ++g) {
+            if (g < ns) {
+                const f32x4 za = *reinterpret_cast<const f32x4*>(zr + c0 + 8 * g);
+                const f32x4 zb = *reinterpret_cast<const f32x4*>(zr + c0 + 8 * g + 4);
+                float p = pieces ? 0.0f : l;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) p = fmaf(za[t], (float)u[g][t], p);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) p = fmaf(zb[t], (float)u[g][4 + t], p);
+                l = pieces ? l + p : p;
+            }
+        }
+    }
+    return l;
+}
+
+struct SelectArgs {
+    const float* z;
+    const uint16_t* zh;
+    const float *cz, *cd;
+    const uint16_t* R2t;
+    const uint16_t* fine;
+    const float* coarse;
+    const float2 *fnorm, *cnorm;
+    int32_t T, Tp, nCp, r, M, k;
+    bool pieces;
+    int32_t* idx;
+    float *gate, *topval;
+};
+
+// Long lists: tokens with more buckets or experts near the threshold than the lists hold (bounds
+// that are loose against the spacing of the logits, ties) go through the same tests again, the whole
+// workgroup on one token: rounds of 32 coarse buckets, of whose fine ones up to 256 pass, and batches of
+// 32 of those.  After each batch the threshold follows the k-th largest of the experts' own lower
+// bounds (a row's norm comes with its product) and of the exact logits so far.
+// Bound by the chain of a batch (about 8 us at r 256).  With a fifth of 4096 tokens coming here (r 256,
+// M 65536, k 16, offsets of variance 0.5 against bounds by the whole norm) 1.25 ms a call, 14.3 with a
+// sweep of all experts by a thread per row in its place; one such token among 16384 at r 64 made a
+// call of 302 us take 750.
+template <int SEG, int NS, bool EXACT, int K>
+__device__ __forceinline__ void select_long(const SelectArgs& a, LongLists<K>& m, int32_t* found,
+                                            const float* zr, float* ex, int32_t t, float theta,
+                                            float cr, float dr) {
+    constexpr int ES = 8 * SEG * NS < 64 ? SEG * NS : 8;  // segments per step of the exact sum
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int32_t r = a.r, M = a.M, k = a.k, nC = 2 * ((M + kSgExperts - 1) / kSgExperts);
+    constexpr int RPL = 64 / SEG;             // rows of a wave's load
+    constexpr int BPW = NS == 1 ? 4 : 2;      // buckets per wave and step
+    constexpr int LOADS = 16 * BPW / RPL;
+    static_assert(LOADS >= 1 && kLongBuckets % (BPW * kSelWaves) == 0 && kLongBuckets * 16 <= 2 * kSelThreads &&
+                  kSelThreads / kSgTiles == 32, "batches");
+    const int seg = lane % SEG;
+    const float rinv = 1.0f / (float)r;
+    // place of a lane's entry in a list counted by found[q]
+    auto put = [&](int q, bool in) __attribute__((always_inline)) {
+        const uint64_t mask = __ballot(in);
+        int b = 0;
+        if (mask && lane == 0) b = atomicAdd(&found[q], (int)__popcll(mask));
+        return __builtin_amdgcn_readfirstlane(b) +
+               (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+    };
+    auto finite = [](float x) __attribute__((always_inline)) {
+        return (__builtin_bit_cast(uint32_t, x) & 0x7F800000u) != 0x7F800000u;
+    };
+    const float c = a.cz[t], d = a.cd[t];
+    // infinite or NaN bounds say nothing: every expert is evaluated
+    bool every = !finite(c) || !finite(d) || !finite(cr) || !finite(dr);
+    if (!finite(theta)) theta = 2.0f * kNoBucket;
+    u32x4 zv[NS];
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+        const bool in = 8 * (SEG * q + seg) < r;
+        zv[q] = *reinterpret_cast<const u32x4*>(a.zh + (int64_t)t * r + (in ? 8 * (SEG * q + seg) : 0));
+        if (!in) zv[q] = u32x4{0u, 0u, 0u, 0u};
+    }
+    int nb = 0;                           // entries of best
+    for (int attempt = 0; attempt < 2 && nb < k; ++attempt) {
+        uint64_t least = 0;               // the k-th of them
+        float lm = 2.0f * kNoBucket;      // this lane's largest lower bound
+        for (int c0 = 0; c0 < nC; c0 += kSelThreads / kSgTiles) {
+            __syncthreads();              // (bucket and found[0] are read no more)
+            if (tid == 0) found[0] = 0;
+            __syncthreads();
+            {
+                const int ci = c0 + tid / kSgTiles, f = c0 * kSgTiles + tid;
+                bool pass = ci < nC;
+                float ub = __builtin_inff();
+                if (pass && !every) {
+                    const float2 cb = a.cnorm[ci];
+                    const float cu = a.coarse[(uint32_t)t * (uint32_t)a.nCp + (uint32_t)ci] +
+                                     fmaf(d, cb.y, c * cb.x);
+                    pass = cu >= theta;
+                    // at best a tie with the k-th, and only larger ids than its
+                    if (least && fmaf(fabsf(cu), 0x1p-20f, cu) <= selection_logit(least) &&
+                        (ci >> 1) * kSgExperts > ~(int32_t)least)
+                        pass = false;
+                    if (pass) {
+                        const float fv = bf16_bits_to_f32(
+                            a.fine[(uint32_t)(ci >> 1) * (16u * (uint32_t)a.Tp) + 16u * (uint32_t)t +
+                                   (uint32_t)(f & 15)]);
+                        const float2 fb = a.fnorm[f];
+                        ub = fv + slack(fv) + fmaf(d, fb.y, c * fb.x);
+                        pass = ub >= theta;
+                    }
+                }
+                const int o = put(0, pass);
+                if (pass) {
+                    m.bucket[o] = f;
+                    m.bound[o] = ub;
+                }
+            }
+            __syncthreads();
+            const int n2 = found[0];
+            for (int b0 = 0; b0 < n2; b0 += kLongBuckets) {
+                if (tid == 0) found[1] = 0;
+                __syncthreads();
+                // rows of the batch, BPW buckets per wave at a time
+                const int be = b0 + kLongBuckets < n2 ? b0 + kLongBuckets : n2;
+                int turn = 0;
+                for (int bw = b0 + BPW * w; bw < be; bw += BPW * kSelWaves) {  // wave-uniform
+                    u32x4 u[LOADS][NS];
+                    int32_t er[LOADS];
+                    bool live[LOADS];
+#pragma unroll
+                    for (int i = 0; i < LOADS; ++i) {
+                        const int q = i * RPL + lane / SEG, b = q % 16;
+                        const int bi = bw + q / 16 < be ? bw + q / 16 : bw;
+                        const int f = m.bucket[bi];
+                        er[i] = (f >> 4) * kSgExperts + (f & 7) * 32 + 4 * ((f >> 3) & 1) +
+                                8 * (b >> 2) + (b & 3);
+                        live[i] = bw + q / 16 < be && er[i] < M && (every || m.bound[bi] >= theta);
+                        const uint16_t* ur = a.R2t + (uint32_t)(live[i] ? er[i] : 0) * (uint32_t)r;
+#pragma unroll
+                        for (int q2 = 0; q2 < NS; ++q2) {
+                            const int col = 8 * (SEG * q2 + seg);
+                            u[i][q2] = *reinterpret_cast<const u32x4*>(ur + (EXACT || col < r ? col : 0));
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < LOADS; ++i) {
+                        float s = 0.0f, ss = 0.0f, su = 0.0f;  // z_hi . u, u . u and u . 1
+#pragma unroll
+                        for (int q2 = 0; q2 < NS; ++q2) {
+                            const bool in = EXACT || 8 * (SEG * q2 + seg) < r;
+#pragma unroll
+                            for (int d = 0; d < 4; ++d) {
+                                const uint32_t ud = in ? u[i][q2][d] : 0u, zd = zv[q2][d];
+                                const bf16x2 up = __builtin_bit_cast(bf16x2, ud);
+                                s = __builtin_amdgcn_fdot2_f32_bf16(up, __builtin_bit_cast(bf16x2, zd), s,
+                                                                    false);
+                                ss = __builtin_amdgcn_fdot2_f32_bf16(up, up, ss, false);
+                                su = __builtin_amdgcn_fdot2_f32_bf16(
+                                    up, __builtin_bit_cast(bf16x2, kOnes), su, false);
+                            }
+                        }
+                        unroll<SEG == 8 ? 3 : (SEG == 4 ? 2 : 1)>([&](auto st) __attribute__((always_inline)) {
+                            s += lane_xor<1 << decltype(st)::value>(s);
+                            ss += lane_xor<1 << decltype(st)::value>(ss);
+                            su += lane_xor<1 << decltype(st)::value>(su);
+                        });
+                        const float2 own = row_bounds(ss, su, rinv);
+                        const float e = fmaf(dr, own.y, cr * own.x);
+                        // the row's lanes keep the lower bounds in turn: 64 distinct experts
+                        if (live[i] && (turn + i) % SEG == seg) lm = fmaxf(lm, s - e);
+                        const bool pass = seg == 0 && live[i] && (every || s + e >= theta);
+                        const int o = put(1, pass);
+                        if (pass) {
+                            m.cand[o] = er[i];
+                            m.cbound[o] = s + e;
+                        }
+                    }
+                    turn += LOADS;
+                }
+                m.wmax[w][lane] = lm;
+                __syncthreads();
+                const int n3 = found[1];
+                float top = m.wmax[0][lane];
+#pragma unroll
+                for (int i = 1; i < kSelWaves; ++i) top = fmaxf(top, m.wmax[i][lane]);
+                top = __shfl(token_sort_desc<64>(top), k - 1, kWave);
+                if (finite(top)) theta = fmaxf(theta, top - fabsf(top) * 0x1p-20f);
+                // exact logits, a thread each
+                for (int i0 = 0; i0 < n3; i0 += kSelThreads) {  // workgroup-uniform
+                    if (tid == 0) found[2] = 0;
+                    __syncthreads();
+                    const int i = i0 + tid;
+                    uint64_t mine = 0;
+                    if (i < n3 && (every || m.cbound[i] >= theta)) {
+                        const int32_t e = m.cand[i];
+                        mine = selection_key(
+                            exact_logit<ES>(a.R2t + (uint32_t)e * (uint32_t)r, zr, r, a.pieces), e);
+                    }
+                    const bool pass = mine > least;  // (never for a thread without an expert)
+                    const int o = put(2, pass);
+                    if (pass) m.fresh[o] = mine;
+                    __syncthreads();
+                    const int nf = found[2];
+                    if (nf) {  // workgroup-uniform: merged into the best by counting
+                        uint64_t last = 0;
+                        int rank = 0, rank2 = 0;
+                        mine = tid < nf ? m.fresh[tid] : 0;
+                        last = tid < nb ? m.best[tid] : 0;
+#pragma unroll 4
+                        for (int q = 0; q < nf; ++q) {
+                            const uint64_t v = m.fresh[q];
+                            rank += v > mine ? 1 : 0;
+                            rank2 += v > last ? 1 : 0;
+                        }
+                        for (int q = 0; q < nb; ++q) rank += m.best[q] > mine ? 1 : 0;
+                        rank2 += tid;
+                        __syncthreads();
+                        if (tid < nf && rank < k) m.best[rank] = mine;
+                        if (tid < nb && rank2 < k) m.best[rank2] = last;
+                        nb = nf + nb < k ? nf + nb : k;
+                        __syncthreads();
+                        if (nb == k) {
+                            least = m.best[k - 1];
+                            const float l = selection_logit(least);
+                            if (finite(l)) theta = fmaxf(theta, l - fabsf(l) * 0x1p-20f);
+                        }
+                    }
+                }
+            }
+        }
+        // fewer than k (bounds spoilt by an overflow): once more without them
+        if (nb < k) {
+            every = true;
+            nb = 0;
+        }
+    }
+    __syncthreads();
+    if (tid < k) {
+        const float l = selection_logit(m.best[tid]);
+        a.idx[(int64_t)t * k + tid] = ~(int32_t)m.best[tid];
+        if (a.topval) a.topval[(int64_t)t * k + tid] = l;
+        ex[tid] = expf(l - selection_logit(m.best[0]));
+    }
+    __syncthreads();
+    if (tid < k) {
+        float sum = 0.0f;  // in rank order
+        for (int i = 0; i < k; ++i) sum += ex[i];
+        a.gate[(int64_t)t * k + tid] = ex[tid] / sum;
+    }
+}
+
 // Steps of a wave, for its tokens side by side (tk = lane / LPT, sub = lane % LPT):
 //  1. theta = the k-th largest of the token's lanes' largest coarse lower bounds;
 //  2. the coarse buckets whose upper bound reaches theta are listed;
@@ -435,13 +722,19 @@ __device__ __forceinline__ float token_sort_desc(float x) {
 // tokens in 53 us; 59 with 64-bit addresses, a reduction per row and ranks by (logit, id) pairs,
 // 92 with the rows staged in LDS, 127 with exact sums for all of them and a token per wave).
 template <int SEG, int NS, bool EXACT, int K, bool COOP>
-__global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
-    const float* __restrict__ z, const uint16_t* __restrict__ zh, const float* __restrict__ cz,
-    const uint16_t* __restrict__ R2t, const uint16_t* __restrict__ fine,
-    const float* __restrict__ coarse, const float* __restrict__ fnorm,
-    const float* __restrict__ cnorm, int32_t T, int32_t Tp, int32_t nCp, int32_t r, int32_t M,
-    int32_t k, bool pieces, int32_t* __restrict__ idx, float* __restrict__ gate,
-    float* __restrict__ topval) {
+__global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(const SelectArgs args) {
+    const float* __restrict__ const z = args.z;
+    const uint16_t* __restrict__ const zh = args.zh;
+    const uint16_t* __restrict__ const R2t = args.R2t;
+    const uint16_t* __restrict__ const fine = args.fine;
+    const float* __restrict__ const coarse = args.coarse;
+    const float2* __restrict__ const fnorm = args.fnorm;
+    const float2* __restrict__ const cnorm = args.cnorm;
+    const int32_t T = args.T, Tp = args.Tp, nCp = args.nCp, r = args.r, M = args.M, k = args.k;
+    const bool pieces = args.pieces;
+    int32_t* __restrict__ const idx = args.idx;
+    float* __restrict__ const gate = args.gate;
+    float* __restrict__ const topval = args.topval;
     using C = SelectCfg<K, COOP>;
     constexpr int LPT = C::LPT, TPW = C::TPW, NCAND = C::NCAND, TOKENS = C::TOKENS;
     constexpr int LANES = COOP ? kSelThreads : LPT;  // lanes of a token in all
@@ -454,6 +747,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         int32_t list1[TOKENS][kSelList];
         int32_t list2[TOKENS][kSelList];
         int32_t list3[TOKENS][NCAND];
+        float wmax[COOP ? 2 : 1][COOP ? kSelWaves : 1][COOP ? 64 : 1];
     };
     __shared__ union {
         Lists lists;                          // of the tokens side by side
@@ -463,8 +757,8 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     auto& list1 = mem.lists.list1;
     auto& list2 = mem.lists.list2;
     auto& list3 = mem.lists.list3;
-    __shared__ float over_theta[TOKENS], over_cr[TOKENS];
-    __shared__ float wmax[COOP ? 2 : 1][kSelWaves][64];
+    auto& wmax = mem.lists.wmax;
+    __shared__ float over_theta[TOKENS], over_cr[TOKENS], over_dr[TOKENS];
     __shared__ int32_t found[4];              // COOP: entries of the four lists
     __shared__ float ex[TOKENS][K];
     __shared__ int32_t over_tok[TOKENS];
@@ -479,40 +773,10 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     const bool ok = tok < T;
     const int32_t nC = 2 * ((M + kSgExperts - 1) / kSgExperts);
     bool over = false;
-    // The logit of expert e for the token with row zr: rank entries in increasing order (pieces: sums
-    // of eight, added up).
-    auto exact = [&](int32_t e, const float* zr) __attribute__((always_inline)) {
-        const uint16_t* ur = R2t + (uint32_t)e * (uint32_t)r;
-        float l = 0.0f;
-        for (int c0 = 0; c0 < r; c0 += 8 * ES) {
-            const int ns = r - c0 < 8 * ES ? (r - c0) / 8 : ES;
-            bf16x8 u[ES];
-#pragma unroll
-            for (int g = 0; g < ES; ++g) u[g] = load_bf16x8(ur + c0 + 8 * (g < ns ? g : 0));
-#pragma unroll
-            for (int g = 0; g < ES; ++g) {
-                if (g < ns) {
-                    const f32x4 za = *reinterpret_cast<const f32x4*>(zr + c0 + 8 * g);
-                    const f32x4 zb = *reinterpret_cast<const f32x4*>(zr + c0 + 8 * g + 4);
-                    float p = pieces ? 0.0f : l;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) p = fmaf(za[t], (float)u[g][t], p);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) p = fmaf(zb[t], (float)u[g][4 + t], p);
-                    l = pieces ? l + p : p;
-                }
-            }
-        }
-        return l;
-    };
-    // the fine maxima are rounded to bf16: 2^-8 relative at most (and subnormals)
-    auto slack = [](float x) __attribute__((always_inline)) {
-        return fmaf(fabsf(x), 0x1.01p-8f, 0x1p-125f);
-    };
     if (COOP && threadIdx.x < 4) found[threadIdx.x] = 0;  // (kth's barrier comes before their use)
     if (tok0 < T) {  // wave-uniform (COOP: always)
         const int32_t tc = ok ? tok : T - 1;  // a wave's second token may lie past T
-        const float c = cz[tc];
+        const float c = args.cz[tc], d = args.cd[tc];
         float zn = 0.0f;                      // ||z||, for the rounding of the bf16 dot products
         uint32_t bits = 0;
         for (int i = 4 * sub; i < r; i += 4 * LPT) {
@@ -592,7 +856,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         constexpr int PIECE = 4 * LANES, ROUND = kSelQ * PIECE;
         const float* crow = coarse + (uint32_t)tc * (uint32_t)nCp;
         const int nround = (nC + ROUND - 1) / ROUND;
-        f32x4 q[kSelQ], nq[kSelQ];
+        f32x4 q[kSelQ], nq[kSelQ][2];
         auto load_round = [&](int rd) __attribute__((always_inline)) {
 #pragma unroll
             for (int m = 0; m < kSelQ; ++m) {
@@ -600,18 +864,21 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
                 if (rd * ROUND + PIECE * m < nC) {  // wave-uniform
                     const int ii = i < nC ? i : 0;
                     q[m] = *reinterpret_cast<const f32x4*>(crow + ii);
-                    nq[m] = *reinterpret_cast<const f32x4*>(cnorm + ii);
+                    nq[m][0] = *reinterpret_cast<const f32x4*>(cnorm + ii);
+                    nq[m][1] = *reinterpret_cast<const f32x4*>(cnorm + ii + 2);
                 }
             }
         };
-        // f(value, c N, bucket, valid) for the round's coarse buckets
+        // f(value, w, bucket, valid) for the round's coarse buckets
         auto scan = [&](int rd, auto&& f) __attribute__((always_inline)) {
 #pragma unroll
             for (int m = 0; m < kSelQ; ++m) {
                 if (rd * ROUND + PIECE * m < nC) {
                     const int i = rd * ROUND + PIECE * m + 4 * gl;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) f(q[m][e], c * nq[m][e], i + e, i + e < nC);
+                    for (int e = 0; e < 4; ++e)
+                        f(q[m][e], fmaf(d, nq[m][e / 2][2 * (e & 1) + 1], c * nq[m][e / 2][2 * (e & 1)]),
+                          i + e, i + e < nC);
                 }
             }
         };
@@ -658,7 +925,8 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
                 // (the maxima of a slab take less than 2^32 bytes)
                 const uint32_t fo = (uint32_t)(cc >> 1) * fstride + 8u * (cc & 1) + fbase;
                 v[m] = bf16_bits_to_f32(fine[fo]);
-                cn[m] = c * fnorm[(uint32_t)(cc * kSgTiles + (sub & 7))];
+                const float2 nb = fnorm[(uint32_t)(cc * kSgTiles + (sub & 7))];
+                cn[m] = fmaf(d, nb.y, c * nb.x);
             }
         };
         float fm = 2.0f * kNoBucket;
@@ -694,11 +962,13 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         zn += lane_xor<8>(zn);
         zn += lane_xor<16>(zn);
         if constexpr (LPT == 64) zn += lane_xor<32>(zn);
-        // a chain of r / 2 dot products, each rounded to 2^-22 relative at worst
-        const float cr = fmaf(sqrtf(zn), 0x1p-14f, c);
+        // a chain of r / 2 dot products, each rounded to 2^-22 relative at worst, against
+        // ||u|| <= N + sqrt(r) m
+        const float cr = fmaf(sqrtf(zn), 0x1p-14f, c), dr = fmaf(sqrtf(zn * (float)r), 0x1p-14f, d);
         if (COOP ? threadIdx.x == 0 : sub == 0) {
             over_theta[j] = theta;
             over_cr[j] = cr;
+            over_dr[j] = dr;
         }
         // ---- 4. refine
         constexpr int BPR = LPT / 16;            // buckets per token and round
@@ -742,7 +1012,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
                 eo = seg >= q * ITB ? eb[q] : eo;
             }
             eo += row_of(seg % ITB, grp);
-            const float nb = fnorm[fo];
+            const float2 nb = fnorm[fo];
             const bool live = rd * BPR + seg / ITB < n2 && eo < M;
             float s = 0.0f;
             // byte offsets fit 32 bits; of a bucket's rows only the first is computed where the row
@@ -808,7 +1078,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
                 rows(std::true_type{});
             else
                 rows(std::false_type{});
-            const bool pass = live && fmaf(cr, nb, s) >= theta;
+            const bool pass = live && fmaf(cr, nb.x, fmaf(dr, nb.y, s)) >= theta;
             const uint64_t mask = __ballot(pass);
             if (mask) {
                 const int o = place(L2{}, mask, n3);
@@ -824,7 +1094,7 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
         for (int i0 = 0; i0 < n3m; i0 += LANES) {
             const int i = i0 + gl;
             const int32_t e = i < n3 ? list3[j][i] : 0;
-            const float l = exact(e, zrow[j]);
+            const float l = exact_logit<ES>(R2t + (uint32_t)e * (uint32_t)r, zrow[j], r, pieces);
             const bool pass = i < n3 && l >= theta;
             const uint64_t mask = __ballot(pass);
             const int o = place(L3{}, mask, nc);  // at most n3 in all
@@ -867,208 +1137,16 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(
     over = ok && over;
     if (COOP ? threadIdx.x == 0 : sub == 0) over_tok[j] = over;
     if (!__syncthreads_or(over)) return;  // workgroup-uniform
-    // Long lists: tokens with more buckets or experts near the threshold than the lists hold (bounds
-    // that are loose against the spacing of the logits, ties) go through the same tests again, the whole
-    // workgroup on one token: rounds of 32 coarse buckets, of whose fine ones up to 256 pass, and batches of
-    // 32 of those.  After each batch the threshold follows the k-th largest of the experts' own lower
-    // bounds (a row's norm comes with its product) and of the exact logits so far.
-    // Bound by the chain of a batch (about 8 us at r 256): 4096 tokens, r 256, M 65536, k 16, offsets of
-    // variance 0.5 (a fifth of the tokens come here) 1.25 ms a call, 14.3 with a sweep of all experts by
-    // a thread per row in its place; one such token among 16384 at r 64 cost 450 us of 750.
-    const int tid = threadIdx.x;
-    LongLists<K>& m = mem.one;
-    constexpr int RPL = 64 / SEG;             // rows of a wave's load
-    constexpr int BPW = NS == 1 ? 4 : 2;      // buckets per wave and step
-    constexpr int LOADS = 16 * BPW / RPL;
-    static_assert(LOADS >= 1 && kLongBuckets % (BPW * kSelWaves) == 0 && kLongBuckets * 16 <= 2 * kSelThreads &&
-                  kSelThreads / kSgTiles == 32, "batches");
-    const int seg = lane % SEG;
-    // place of a lane's entry in a list counted by found[q]
-    auto put = [&](int q, bool in) __attribute__((always_inline)) {
-        const uint64_t mask = __ballot(in);
-        int b = 0;
-        if (mask && lane == 0) b = atomicAdd(&found[q], (int)__popcll(mask));
-        return __builtin_amdgcn_readfirstlane(b) +
-               (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-    };
-    auto finite = [](float x) __attribute__((always_inline)) {
-        return (__builtin_bit_cast(uint32_t, x) & 0x7F800000u) != 0x7F800000u;
-    };
-    for (int jt = 0; jt < TOKENS; ++jt) {
-        if (!over_tok[jt]) continue;          // workgroup-uniform
-        const int32_t t = (int32_t)blockIdx.x * TOKENS + jt;
-        const float c = cz[t], cr = over_cr[jt];
-        float theta = over_theta[jt];
-        // infinite or NaN bounds say nothing: every expert is evaluated
-        bool every = !finite(c) || !finite(cr);
-        if (!finite(theta)) theta = 2.0f * kNoBucket;
-        u32x4 zv[NS];
-#pragma unroll
-        for (int q = 0; q < NS; ++q) {
-            const bool in = 8 * (SEG * q + seg) < r;
-            zv[q] = *reinterpret_cast<const u32x4*>(zh + (int64_t)t * r + (in ? 8 * (SEG * q + seg) : 0));
-            if (!in) zv[q] = u32x4{0u, 0u, 0u, 0u};
-        }
-        int nb = 0;                           // entries of best
-        for (int attempt = 0; attempt < 2 && nb < k; ++attempt) {
-            uint64_t least = 0;               // the k-th of them
-            float lm = 2.0f * kNoBucket;      // this lane's largest lower bound
-            for (int c0 = 0; c0 < nC; c0 += kSelThreads / kSgTiles) {
-                __syncthreads();              // (bucket and found[0] are read no more)
-                if (tid == 0) found[0] = 0;
-                __syncthreads();
-                {
-                    const int ci = c0 + tid / kSgTiles, f = c0 * kSgTiles + tid;
-                    bool pass = ci < nC;
-                    float ub = __builtin_inff();
-                    if (pass && !every) {
-                        const float cu = coarse[(uint32_t)t * (uint32_t)nCp + (uint32_t)ci] + c * cnorm[ci];
-                        pass = cu >= theta;
-                        // at best a tie with the k-th, and only larger ids than its
-                        if (least && fmaf(fabsf(cu), 0x1p-20f, cu) <= selection_logit(least) &&
-                            (ci >> 1) * kSgExperts > ~(int32_t)least)
-                            pass = false;
-                        if (pass) {
-                            const float fv = bf16_bits_to_f32(
-                                fine[(uint32_t)(ci >> 1) * (16u * (uint32_t)Tp) + 16u * (uint32_t)t +
-                                     (uint32_t)(f & 15)]);
-                            ub = fv + slack(fv) + c * fnorm[f];
-                            pass = ub >= theta;
-                        }
-                    }
-                    const int o = put(0, pass);
-                    if (pass) {
-                        m.bucket[o] = f;
-                        m.bound[o] = ub;
-                    }
-                }
-                __syncthreads();
-                const int n2 = found[0];
-                for (int b0 = 0; b0 < n2; b0 += kLongBuckets) {
-                    if (tid == 0) found[1] = 0;
-                    __syncthreads();
-                    // rows of the batch, BPW buckets per wave at a time
-                    const int be = b0 + kLongBuckets < n2 ? b0 + kLongBuckets : n2;
-                    int turn = 0;
-                    for (int bw = b0 + BPW * w; bw < be; bw += BPW * kSelWaves) {  // wave-uniform
-                        u32x4 u[LOADS][NS];
-                        int32_t er[LOADS];
-                        bool live[LOADS];
-#pragma unroll
-                        for (int i = 0; i < LOADS; ++i) {
-                            const int q = i * RPL + lane / SEG, b = q % 16;
-                            const int bi = bw + q / 16 < be ? bw + q / 16 : bw;
-                            const int f = m.bucket[bi];
-                            er[i] = (f >> 4) * kSgExperts + (f & 7) * 32 + 4 * ((f >> 3) & 1) +
-                                    8 * (b >> 2) + (b & 3);
-                            live[i] = bw + q / 16 < be && er[i] < M && (every || m.bound[bi] >= theta);
-                            const uint16_t* ur = R2t + (uint32_t)(live[i] ? er[i] : 0) * (uint32_t)r;
-#pragma unroll
-                            for (int q2 = 0; q2 < NS; ++q2) {
-                                const int col = 8 * (SEG * q2 + seg);
-                                u[i][q2] = *reinterpret_cast<const u32x4*>(ur + (EXACT || col < r ? col : 0));
-                            }
-                        }
-#pragma unroll
-                        for (int i = 0; i < LOADS; ++i) {
-                            float s = 0.0f, ss = 0.0f;  // z_hi . u and u . u
-#pragma unroll
-                            for (int q2 = 0; q2 < NS; ++q2) {
-                                const bool in = EXACT || 8 * (SEG * q2 + seg) < r;
-#pragma unroll
-                                for (int d = 0; d < 4; ++d) {
-                                    const uint32_t ud = in ? u[i][q2][d] : 0u, zd = zv[q2][d];
-                                    const bf16x2 up = __builtin_bit_cast(bf16x2, ud);
-                                    s = __builtin_amdgcn_fdot2_f32_bf16(up, __builtin_bit_cast(bf16x2, zd), s,
-                                                                        false);
-                                    ss = __builtin_amdgcn_fdot2_f32_bf16(up, up, ss, false);
-                                }
-                            }
-                            unroll<SEG == 8 ? 3 : (SEG == 4 ? 2 : 1)>([&](auto st) __attribute__((always_inline)) {
-                                s += lane_xor<1 << decltype(st)::value>(s);
-                                ss += lane_xor<1 << decltype(st)::value>(ss);
-                            });
-                            const float e = cr * (sqrtf(ss) * (1.0f + 0x1p-20f));
-                            // the row's lanes keep the lower bounds in turn: 64 distinct experts
-                            if (live[i] && (turn + i) % SEG == seg) lm = fmaxf(lm, s - e);
-                            const bool pass = seg == 0 && live[i] && (every || s + e >= theta);
-                            const int o = put(1, pass);
-                            if (pass) {
-                                m.cand[o] = er[i];
-                                m.cbound[o] = s + e;
-                            }
-                        }
-                        turn += LOADS;
-                    }
-                    wmax[0][w][lane] = lm;
-                    __syncthreads();
-                    const int n3 = found[1];
-                    float top = wmax[0][0][lane];
-#pragma unroll
-                    for (int i = 1; i < kSelWaves; ++i) top = fmaxf(top, wmax[0][i][lane]);
-                    top = __shfl(token_sort_desc<64>(top), k - 1, kWave);
-                    if (finite(top)) theta = fmaxf(theta, top - fabsf(top) * 0x1p-20f);
-                    // exact logits, a thread each
-                    for (int i0 = 0; i0 < n3; i0 += kSelThreads) {  // workgroup-uniform
-                        if (tid == 0) found[2] = 0;
-                        __syncthreads();
-                        const int i = i0 + tid;
-                        uint64_t mine = 0;
-                        if (i < n3 && (every || m.cbound[i] >= theta))
-                            mine = selection_key(exact(m.cand[i], zrow[jt]), m.cand[i]);
-                        const bool pass = mine > least;  // (never for a thread without an expert)
-                        const int o = put(2, pass);
-                        if (pass) m.fresh[o] = mine;
-                        __syncthreads();
-                        const int nf = found[2];
-                        if (nf) {  // workgroup-uniform: merged into the best by counting
-                            uint64_t last = 0;
-                            int rank = 0, rank2 = 0;
-                            mine = tid < nf ? m.fresh[tid] : 0;
-                            last = tid < nb ? m.best[tid] : 0;
-#pragma unroll 4
-                            for (int q = 0; q < nf; ++q) {
-                                const uint64_t v = m.fresh[q];
-                                rank += v > mine ? 1 : 0;
-                                rank2 += v > last ? 1 : 0;
-                            }
-                            for (int q = 0; q < nb; ++q) rank += m.best[q] > mine ? 1 : 0;
-                            rank2 += tid;
-                            __syncthreads();
-                            if (tid < nf && rank < k) m.best[rank] = mine;
-                            if (tid < nb && rank2 < k) m.best[rank2] = last;
-                            nb = nf + nb < k ? nf + nb : k;
-                            __syncthreads();
-                            if (nb == k) {
-                                least = m.best[k - 1];
-                                const float l = selection_logit(least);
-                                if (finite(l)) theta = fmaxf(theta, l - fabsf(l) * 0x1p-20f);
-                            }
-                        }
-                    }
-                }
-            }
-            // fewer than k (bounds spoilt by an overflow): once more without them
-            if (nb < k) {
-                every = true;
-                nb = 0;
-            }
-        }
-        __syncthreads();
-        if (tid < k) {
-            const float l = selection_logit(m.best[tid]);
-            idx[(int64_t)t * k + tid] = ~(int32_t)m.best[tid];
-            if (topval) topval[(int64_t)t * k + tid] = l;
-            ex[jt][tid] = expf(l - selection_logit(m.best[0]));
-        }
-        __syncthreads();
-        if (tid < k) {
-            float sum = 0.0f;  // in rank order
-            for (int i = 0; i < k; ++i) sum += ex[jt][i];
-            gate[(int64_t)t * k + tid] = ex[jt][tid] / sum;
-        }
-    }
+    // The arguments are read again: held in registers over the steps above they would be spilled there
+    // (T 32768, r 64, M 16384: 61.6 us, 60.2 so).
+    auto kernarg = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kernarg));
+    const SelectArgs& again = *(const SelectArgs*)kernarg;
+    for (int jt = 0; jt < TOKENS; ++jt)
+        if (over_tok[jt])  // workgroup-uniform
+            select_long<SEG, NS, EXACT, K>(again, mem.one, found, zrow[jt], ex[jt],
+                                           (int32_t)blockIdx.x * TOKENS + jt, over_theta[jt], over_cr[jt],
+                                           over_dr[jt]);
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -1132,8 +1210,8 @@ SweepGrid sweep_grid(int32_t rc, int32_t T, int32_t nsg) {
 
 template <int RC>
 void launch_sweep(const SweepGrid& g, const BucketArgs& a, int32_t T, const uint16_t* zh,
-                  int32_t Tp, int32_t nCp, uint32_t* fine, float* coarse, float* fnorm,
-                  float* cnorm, int32_t* hist, hipStream_t st) {
+                  int32_t Tp, int32_t nCp, uint32_t* fine, float* coarse, float2* fnorm,
+                  float2* cnorm, int32_t* hist, hipStream_t st) {
     hipLaunchKernelGGL((bucket_sweep_kernel<RC>), dim3((unsigned)g.chunks * (unsigned)g.splits),
                        dim3(kSweepThreads), 0, st, zh, a.R2t, T, a.r, a.M, g.chunks, g.splits, g.ew,
                        Tp, nCp, fine, coarse, fnorm, cnorm, hist);
@@ -1141,20 +1219,21 @@ void launch_sweep(const SweepGrid& g, const BucketArgs& a, int32_t T, const uint
 
 template <int SEG, int NS, bool EXACT, int K, bool COOP>
 void launch_select(const BucketArgs& a, int64_t t0, int32_t T, int32_t Tp, int32_t nCp,
-                   const uint32_t* fine, const float* coarse, const float* fnorm, const float* cnorm,
+                   const uint32_t* fine, const float* coarse, const float2* fnorm, const float2* cnorm,
                    hipStream_t st) {
     constexpr int TOK = SelectCfg<K, COOP>::TOKENS;
-    hipLaunchKernelGGL((bucket_select_kernel<SEG, NS, EXACT, K, COOP>), dim3((unsigned)((T + TOK - 1) / TOK)),
-                       dim3(kSelThreads), 0, st, a.z + t0 * a.r, a.zhi + t0 * a.r, a.cz + t0,
-                       a.R2t, reinterpret_cast<const uint16_t*>(fine), coarse, fnorm, cnorm, T, Tp,
-                       nCp, a.r, a.M, a.k, a.pieces, a.idx + t0 * a.k, a.gate + t0 * a.k,
-                       a.topval ? a.topval + t0 * a.k : nullptr);
+    const SelectArgs args{a.z + t0 * a.r, a.zhi + t0 * a.r, a.cz + t0, a.cd + t0, a.R2t,
+                          reinterpret_cast<const uint16_t*>(fine), coarse, fnorm, cnorm, T, Tp, nCp, a.r,
+                          a.M, a.k, a.pieces, a.idx + t0 * a.k, a.gate + t0 * a.k,
+                          a.topval ? a.topval + t0 * a.k : nullptr};
+    hipLaunchKernelGGL((bucket_select_kernel<SEG, NS, EXACT, K, COOP>),
+                       dim3((unsigned)((T + TOK - 1) / TOK)), dim3(kSelThreads), 0, st, args);
 }
 
 template <int SEG, int NS, bool EXACT>
 void launch_select_k(const BucketArgs& a, int64_t t0, int32_t T, int32_t Tp, int32_t nCp,
-                     const uint32_t* fine, const float* coarse, const float* fnorm,
-                     const float* cnorm, hipStream_t st) {
+                     const uint32_t* fine, const float* coarse, const float2* fnorm,
+                     const float2* cnorm, hipStream_t st) {
     constexpr int S4 = SEG < 4 ? 4 : SEG;  // 64 lanes per token: at most 16 rows per load
     constexpr bool X4 = EXACT && SEG >= 4;
 #define MORE_SELECT(S, X, K, COOP) \
@@ -1195,15 +1274,17 @@ bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t z_bytes
     const int64_t even = ((T + ns - 1) / ns + 255) / 256 * 256;
     p->slab = even < slab ? even : slab;
     size_t o = 0;
+    p->off_cd = o;
+    o += align256((size_t)T * sizeof(float));
     p->off_fine = o;
     o += align256((size_t)nsg * p->slab * 32);
     p->off_coarse = o;
     p->nCp = (2 * nsg + 3) / 4 * 4;
     o += align256((size_t)p->slab * p->nCp * sizeof(float));
     p->off_fnorm = o;
-    o += align256((size_t)nsg * 16 * sizeof(float));
+    o += align256((size_t)nsg * 16 * sizeof(float2));
     p->off_cnorm = o;
-    o += align256((size_t)p->nCp * sizeof(float));
+    o += align256((size_t)p->nCp * sizeof(float2));
     p->bytes = o;
     return true;
 }
@@ -1212,8 +1293,8 @@ hipError_t bucket_launch(const BucketPlan& p, const BucketArgs& a, void* scratch
     char* ws = static_cast<char*>(scratch);
     uint32_t* fine = reinterpret_cast<uint32_t*>(ws + p.off_fine);
     float* coarse = reinterpret_cast<float*>(ws + p.off_coarse);
-    float* fnorm = reinterpret_cast<float*>(ws + p.off_fnorm);
-    float* cnorm = reinterpret_cast<float*>(ws + p.off_cnorm);
+    float2* fnorm = reinterpret_cast<float2*>(ws + p.off_fnorm);
+    float2* cnorm = reinterpret_cast<float2*>(ws + p.off_cnorm);
     const int32_t nsg = (a.M + kSgExperts - 1) / kSgExperts;
     const int32_t rc = sweep_rc(a.r);
     const int32_t Tp = (int32_t)p.slab;

@@ -61,12 +61,13 @@ hipError_t fullrank_launch(const FullrankPlan& plan, const uint16_t* x, const ui
                            int64_t T, int32_t h, int32_t M, int32_t k, int32_t* idx, float* gate,
                            float* topval, void* workspace, hipStream_t stream, int* blas_status);
 
-// z = x R1, fp32 [T][r] at z, with z_hi = bf16(z) [T][r] and the screening scale cz [T], for callers other
-// than the routes; r a multiple of 16 up to 256.  scratch: zpass_workspace_bytes (the h-split
+// z = x R1, fp32 [T][r] at z, with z_hi = bf16(z) [T][r] and the screening scales cz and cd (nullable) [T],
+// for callers other than the routes; r a multiple of 16 up to 256.  scratch: zpass_workspace_bytes (the h-split
 // partials).
 size_t zpass_workspace_bytes(int64_t T, int32_t h, int32_t r);
 hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
-                        float* z, uint16_t* zhi, float* cz, void* scratch, hipStream_t stream);
+                        float* z, uint16_t* zhi, float* cz, float* cd, void* scratch,
+                        hipStream_t stream);
 
 // The z pass without the sum over its h splits, for a caller whose next kernel takes it: returns the
 // partials in *parts, [*splits][T][r], to be added in order (one split: *parts == z).

@@ -98,7 +98,8 @@ __global__ __launch_bounds__(256) void zpass_kernel(const uint16_t* __restrict__
                                                     int32_t zblocks, int32_t hsplit,
                                                     float* __restrict__ gnorm,
                                                     uint16_t* __restrict__ zhi_out,
-                                                    float* __restrict__ c_out) {
+                                                    float* __restrict__ c_out,
+                                                    float* __restrict__ d_out) {
     // Workgroups [0, zblocks * hsplit) compute z (token block bx % zblocks, h split
     // bx / zblocks); the rest compute group norms.
     if ((int)blockIdx.x >= zblocks * hsplit) {  // workgroup-uniform: a group-norm workgroup
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(256) void zpass_kernel(const uint16_t* __restrict__
     // Lane (n, half) holds z[n][16 c + 8 half + 0..7] in accumulator elements 8 c2 .. 8 c2 + 7
     // of tile pt (c = 2 pt + c2).  Without an h split the z pass also writes the screening
     // operands: z_hi = bf16(z) in the same layout and the error scale c of the token.
-    float lo2 = 0.0f, hi2 = 0.0f;
+    float lo2 = 0.0f, hi2 = 0.0f, lo1 = 0.0f;
     float* zrow = zout + ((int64_t)split * T + (tok_ok ? tok : 0)) * r + 8 * half;
     uint16_t* hrow = zhi_out + (tok_ok ? tok : 0) * (int64_t)r + 8 * half;
 #pragma unroll
@@ -248,6 +249,7 @@ __global__ __launch_bounds__(256) void zpass_kernel(const uint16_t* __restrict__
                     const float lf = v - hf;
                     hi2 = fmaf(hf, hf, hi2);
                     lo2 = fmaf(lf, lf, lo2);
+                    lo1 += lf;
                 }
                 if (tok_ok) {
                     *reinterpret_cast<f32x4*>(zrow + 16 * c) = lo4;
@@ -261,17 +263,22 @@ __global__ __launch_bounds__(256) void zpass_kernel(const uint16_t* __restrict__
     if (hsplit == 1) {
         hi2 += __shfl_xor(hi2, 32, kWave);
         lo2 += __shfl_xor(lo2, 32, kWave);
-        if (tok_ok && half == 0) c_out[tok] = screen_scale(lo2, hi2, r);
+        lo1 += __shfl_xor(lo1, 32, kWave);
+        if (tok_ok && half == 0) {
+            c_out[tok] = screen_scale(lo2, hi2, r);
+            if (d_out) d_out[tok] = mean_scale(lo1, hi2, r);
+        }
     }
 }
 
 // Sums the h-split partials of z (per element, splits in increasing order), then writes z,
-// z_hi = bf16(z) and the token's error scale c.  256 threads = 256 / r tokens, one thread per
+// z_hi = bf16(z) and the token's error scales c and d (d_out nullable).  256 threads = 256 / r tokens, one thread per
 // element; the r threads of a token are consecutive lanes of one wave.
 __global__ __launch_bounds__(256) void zreduce_kernel(const float* __restrict__ zparts,
                                                       float* __restrict__ z,
                                                       uint16_t* __restrict__ zhi,
-                                                      float* __restrict__ cz, int32_t T,
+                                                      float* __restrict__ cz,
+                                                      float* __restrict__ d_out, int32_t T,
                                                       int32_t r, int32_t splits) {
     const int64_t n = (int64_t)T * r;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -292,15 +299,19 @@ __global__ __launch_bounds__(256) void zreduce_kernel(const float* __restrict__ 
     const __bf16 hb = (__bf16)s;
     const float hf = (float)hb;
     const float lf = s - hf;
-    float hi2 = hf * hf, lo2 = lf * lf;
+    float hi2 = hf * hf, lo2 = lf * lf, lo1 = lf;
     for (int m = 1; m < r; m <<= 1) {
         hi2 += __shfl_xor(hi2, m, kWave);
         lo2 += __shfl_xor(lo2, m, kWave);
+        lo1 += __shfl_xor(lo1, m, kWave);
     }
     if (ok) {
         z[i] = s;
         zhi[i] = __builtin_bit_cast(uint16_t, hb);
-        if (i % r == 0) cz[i / r] = screen_scale(lo2, hi2, r);
+        if (i % r == 0) {
+            cz[i / r] = screen_scale(lo2, hi2, r);
+            if (d_out) d_out[i / r] = mean_scale(lo1, hi2, r);
+        }
     }
 }
 
@@ -309,13 +320,14 @@ __global__ __launch_bounds__(256) void zreduce_kernel(const float* __restrict__ 
 __global__ __launch_bounds__(256) void zreduce_wide_kernel(const float* __restrict__ zparts,
                                                            float* __restrict__ z,
                                                            uint16_t* __restrict__ zhi,
-                                                           float* __restrict__ cz, int32_t T,
+                                                           float* __restrict__ cz,
+                                                           float* __restrict__ d_out, int32_t T,
                                                            int32_t r, int32_t splits) {
     const int lane = threadIdx.x & 63;
     const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= T) return;  // wave-uniform
     const int64_t n = (int64_t)T * r;
-    float hi2 = 0.0f, lo2 = 0.0f;
+    float hi2 = 0.0f, lo2 = 0.0f, lo1 = 0.0f;
     for (int j = lane; j < r; j += 64) {
         const int64_t i = t * r + j;
         float s = 0.0f;
@@ -332,25 +344,30 @@ __global__ __launch_bounds__(256) void zreduce_wide_kernel(const float* __restri
         const float hf = (float)hb, lf = s - hf;
         hi2 = fmaf(hf, hf, hi2);
         lo2 = fmaf(lf, lf, lo2);
+        lo1 += lf;
         z[i] = s;
         zhi[i] = __builtin_bit_cast(uint16_t, hb);
     }
     for (int m = 1; m < 64; m <<= 1) {
         hi2 += __shfl_xor(hi2, m, kWave);
         lo2 += __shfl_xor(lo2, m, kWave);
+        lo1 += __shfl_xor(lo1, m, kWave);
     }
-    if (lane == 0) cz[t] = screen_scale(lo2, hi2, r);
+    if (lane == 0) {
+        cz[t] = screen_scale(lo2, hi2, r);
+        if (d_out) d_out[t] = mean_scale(lo1, hi2, r);
+    }
 }
 
-static void launch_zreduce(const float* zparts, float* z, uint16_t* zhi, float* cz, int64_t T,
-                           int32_t r, int32_t splits, hipStream_t st) {
+static void launch_zreduce(const float* zparts, float* z, uint16_t* zhi, float* cz, float* d_out,
+                           int64_t T, int32_t r, int32_t splits, hipStream_t st) {
     if (r == 16 || r == 32 || r == 64) {
         const int64_t n = T * r;
         hipLaunchKernelGGL(zreduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                           zparts, z, zhi, cz, (int32_t)T, r, splits);
+                           zparts, z, zhi, cz, d_out, (int32_t)T, r, splits);
     } else {
         hipLaunchKernelGGL(zreduce_wide_kernel, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, st,
-                           zparts, z, zhi, cz, (int32_t)T, r, splits);
+                           zparts, z, zhi, cz, d_out, (int32_t)T, r, splits);
     }
 }
 
@@ -1255,7 +1272,7 @@ bool lowrank_make_plan(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k, in
 template <int RT>
 static void launch_zpass(const LowrankPlan& p, const uint16_t* x, const uint16_t* R1t, float* zparts,
                          int64_t T, int32_t h, int32_t r, const uint16_t* R2t, int32_t M,
-                         float* gnorm, uint16_t* zhi, float* cz, hipStream_t st) {
+                         float* gnorm, uint16_t* zhi, float* cz, float* d_out, hipStream_t st) {
     const int64_t zblocks = (T + kZTokens - 1) / kZTokens;
     // group-norm workgroups, unless the expert-resident route runs one token split: then its
     // screen kernel computes the norms from its LDS chunk (each chunk is loaded once)
@@ -1268,7 +1285,7 @@ static void launch_zpass(const LowrankPlan& p, const uint16_t* x, const uint16_t
     constexpr int D = 2;
     hipLaunchKernelGGL((zpass_kernel<RT, D>), grid, dim3(256), 0, st, x, R1t, zparts, (int32_t)T,
                        h, r, p.steps_per_split, R2t, M, (int32_t)zblocks, p.hsplit, gnorm, zhi,
-                       cz);
+                       cz, d_out);
 }
 
 struct RouteArgs {
@@ -1356,15 +1373,15 @@ size_t zpass_workspace_bytes(int64_t T, int32_t h, int32_t r) {
 
 // The z pass alone, into zparts (z itself with one split).
 static void zpass_only(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
-                       float* zparts, uint16_t* zhi, float* cz, int32_t sps, int32_t hs,
-                       hipStream_t st) {
+                       float* zparts, uint16_t* zhi, float* cz, float* d_out, int32_t sps,
+                       int32_t hs, hipStream_t st) {
     const int64_t zblocks = (T + kZTokens - 1) / kZTokens;
     const dim3 grid((unsigned)(zblocks * hs));  // no group-norm workgroups
     constexpr int D = 2;
     // tiles of 32 rank rows: 1, 2, 4 or 8 (rows past r are computed and dropped)
 #define MORE_ZPASS(RT)                                                                           \
     hipLaunchKernelGGL((zpass_kernel<RT, D>), grid, dim3(256), 0, st, x, R1t, zparts, (int32_t)T, \
-                       h, r, sps, nullptr, 0, (int32_t)zblocks, hs, nullptr, zhi, cz)
+                       h, r, sps, nullptr, 0, (int32_t)zblocks, hs, nullptr, zhi, cz, d_out)
     if (r <= 32)
         MORE_ZPASS(1);
     else if (r <= 64)
@@ -1377,12 +1394,13 @@ static void zpass_only(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_
 }
 
 hipError_t zpass_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32_t h, int32_t r,
-                        float* z, uint16_t* zhi, float* cz, void* scratch, hipStream_t st) {
+                        float* z, uint16_t* zhi, float* cz, float* d_out, void* scratch,
+                        hipStream_t st) {
     int32_t sps, hs;
     zpass_split(T, h, &sps, &hs);
     float* zparts = hs > 1 ? static_cast<float*>(scratch) : z;
-    zpass_only(x, R1t, T, h, r, zparts, zhi, cz, sps, hs, st);
-    if (hs > 1) launch_zreduce(zparts, z, zhi, cz, T, r, hs, st);
+    zpass_only(x, R1t, T, h, r, zparts, zhi, cz, d_out, sps, hs, st);
+    if (hs > 1) launch_zreduce(zparts, z, zhi, cz, d_out, T, r, hs, st);
     return hipGetLastError();
 }
 
@@ -1401,7 +1419,7 @@ hipError_t zparts_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int3
     const size_t o2 = o1 + align256((size_t)T * r * sizeof(uint16_t));
     float* zparts = hs > 1 ? reinterpret_cast<float*>(s) : z;
     zpass_only(x, R1t, T, h, r, zparts, reinterpret_cast<uint16_t*>(s + o1),
-               reinterpret_cast<float*>(s + o2), sps, hs, st);
+               reinterpret_cast<float*>(s + o2), nullptr, sps, hs, st);
     *parts = zparts;
     *splits = hs;
     return hipGetLastError();
@@ -1413,7 +1431,7 @@ hipError_t zonly_launch(const uint16_t* x, const uint16_t* R1t, int64_t T, int32
     const size_t o1 = zpass_workspace_bytes(T, h, r);
     const size_t o2 = o1 + align256((size_t)T * r * sizeof(uint16_t));
     return zpass_launch(x, R1t, T, h, r, z, reinterpret_cast<uint16_t*>(s + o1),
-                        reinterpret_cast<float*>(s + o2), s, st);
+                        reinterpret_cast<float*>(s + o2), nullptr, s, st);
 }
 
 hipError_t lowrank_launch(const LowrankPlan& p, const uint16_t* x, const uint16_t* R1t,
@@ -1436,6 +1454,7 @@ hipError_t lowrank_launch(const LowrankPlan& p, const uint16_t* x, const uint16_
     a.z = reinterpret_cast<float*>(ws + p.off_z);
     a.zhi = reinterpret_cast<uint16_t*>(ws + p.off_zhi);
     a.cz = reinterpret_cast<float*>(ws + p.off_cz);
+    float* cd = p.bucket ? reinterpret_cast<float*>(ws + p.off_bk + p.bk.off_cd) : nullptr;
     a.R2t = R2t;
     a.T = (int32_t)T;
     a.M = M;
@@ -1451,17 +1470,17 @@ hipError_t lowrank_launch(const LowrankPlan& p, const uint16_t* x, const uint16_
     a.topval = topval;
 
     switch (p.RT) {
-        case 1: launch_zpass<1>(p, x, R1t, zparts, T, h, r, R2t, M, a.gnorm, a.zhi, a.cz, st);
+        case 1: launch_zpass<1>(p, x, R1t, zparts, T, h, r, R2t, M, a.gnorm, a.zhi, a.cz, cd, st);
             break;
-        case 2: launch_zpass<2>(p, x, R1t, zparts, T, h, r, R2t, M, a.gnorm, a.zhi, a.cz, st);
+        case 2: launch_zpass<2>(p, x, R1t, zparts, T, h, r, R2t, M, a.gnorm, a.zhi, a.cz, cd, st);
             break;
         default: return hipErrorInvalidValue;
     }
     if (p.hsplit > 1) {
-        launch_zreduce(zparts, const_cast<float*>(a.z), a.zhi, a.cz, T, r, p.hsplit, st);
+        launch_zreduce(zparts, const_cast<float*>(a.z), a.zhi, a.cz, cd, T, r, p.hsplit, st);
     }
     if (p.bucket) {
-        const BucketArgs b{a.z, a.zhi, a.cz, R2t, T, r, M, k, false, counts, idx, gate, topval};
+        const BucketArgs b{a.z, a.zhi, a.cz, cd, R2t, T, r, M, k, false, counts, idx, gate, topval};
         return bucket_launch(p.bk, b, ws + p.off_bk, st);
     }
     bool ok = false;

@@ -33,6 +33,12 @@ __device__ __forceinline__ float screen_scale(float lo2, float hi2, int r) {
     return fmaxf((sqrtf(lo2) + (float)r * 0x1p-23f * sqrtf(hi2)) * (1.0f + 0x1p-10f), 0x1p-126f);
 }
 
+// The same against a row split as u = mu 1 + u' (mu its mean): |s_e - l_e| <= c ||u'|| + d |mu| with
+// d = (|sum z_lo| + 2 r^(3/2) 2^-23 ||z_hi||) (1 + 2^-10).  (z_lo . u = z_lo . u' + mu sum z_lo; the
+// second term covers the rounding of z_hi . u, as ||u|| <= ||u'|| + sqrt(r) |mu|, and that of the sum.)
+__device__ __forceinline__ float mean_scale(float losum, float hi2, int r) {
+    return (fabsf(losum) + (float)r * sqrtf((float)r * hi2) * 0x1p-22f) * (1.0f + 0x1p-10f);
+}
 
 constexpr float kPhantomNorm = 0x1p100f;  // norm bound of a 4-expert group reaching past M
 

@@ -138,10 +138,11 @@ hipError_t wide_launch(const WidePlan& p, const uint16_t* x, const uint16_t* R1t
     float* z = reinterpret_cast<float*>(ws + p.off_z);
     uint16_t* zhi = reinterpret_cast<uint16_t*>(ws + p.off_zhi);
     float* cz = reinterpret_cast<float*>(ws + p.off_cz);
-    hipError_t e = zpass_launch(x, R1t, T, h, r, z, zhi, cz, ws + p.off_zscratch, st);
+    float* cd = p.bucket ? reinterpret_cast<float*>(ws + p.off_bk + p.bk.off_cd) : nullptr;
+    hipError_t e = zpass_launch(x, R1t, T, h, r, z, zhi, cz, cd, ws + p.off_zscratch, st);
     if (e != hipSuccess) return e;
     if (p.bucket) {
-        const BucketArgs b{z, zhi, cz, R2t, T, r, M, k, true, counts, idx, gate, topval};
+        const BucketArgs b{z, zhi, cz, cd, R2t, T, r, M, k, true, counts, idx, gate, topval};
         return bucket_launch(p.bk, b, ws + p.off_bk, st);
     }
     uint16_t* zs = reinterpret_cast<uint16_t*>(ws + p.off_zs);

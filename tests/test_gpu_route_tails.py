@@ -79,3 +79,18 @@ def test_tying_experts(shape):
         idx, gate, _, _ = route_lowrank(inp, k, tag="equal experts")
         assert np.array_equal(idx, np.broadcast_to(np.arange(k, dtype=np.int32), (T, k)))
         assert np.allclose(gate, 1.0 / k, atol=1e-6)
+@pytest.mark.parametrize("T,r,M,k", [(1500, 256, 16384, 32), (1500, 128, 40000, 32), (700, 256, 40000, 16),
+                                     (2100, 256, 9000, 8)])
+def test_expert_offsets_at_long_ranks(T, r, M, k):
+    """Offsets of the experts' rows (a skewed load) give them large norms, so that for tokens whose offsets
+    cancel many buckets lie within the screening bounds of the threshold."""
+    h = 128
+    plain = _us(make_inputs(T, h, r, M, seed=1), k)
+    inp = make_inputs(T, h, r, M, seed=2, expert_bias_var=0.5)
+    skewed = _us(inp, k)
+    print("[time] plain %.1f us, offsets %.1f us" % (plain, skewed), flush=True)
+    assert skewed < 5.0 * plain  # 10 to 40 times slower with a sweep of all experts for such tokens
+    idx, gate, topval, _ = route_lowrank(inp, k, tag="offsets")
+    rep = parity.evaluate(inp.x, inp.R1, inp.R2, k, idx, gate, topval,
+                          rows=np.arange(0, T, 3, dtype=np.int64))
+    assert rep.ok(), str(rep)

@@ -69,6 +69,8 @@ struct SweepCfg {
     // more rank chunks the operands of both leave no registers for it (the SIMD's other wave
     // fills the gap)
     static constexpr bool HALVES = RC <= 8;
+    // coarse maxima are stored for four super-groups at a time (32 bytes per token)
+    static constexpr bool QUADS = SGS >= 4;
     static_assert(SGS >= 1, "one super-group fits");
     __device__ static constexpr int pos(int e, int s) {  // position of segment s of row e
         return POW2 ? (s ^ ((e / (16 / (SPR < 16 ? SPR : 16))) % SPR)) : s;
@@ -103,7 +105,7 @@ __device__ __forceinline__ float max16(const f32x16& a) {
 template <int RC>
 __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
     const uint16_t* __restrict__ zh, const uint16_t* __restrict__ R2t, int32_t T, int32_t r,
-    int32_t M, int32_t chunks, int32_t splits, int32_t ew, int32_t Tp, int32_t nCp,
+    int32_t M, int32_t chunks, int32_t splits, int32_t ew, int32_t unit, int32_t Tp, int32_t nCp,
     uint32_t* __restrict__ fine, float* __restrict__ coarse, float2* __restrict__ fnorm,
     float2* __restrict__ cnorm, int32_t* __restrict__ hist) {
     using C = SweepCfg<RC>;
@@ -117,8 +119,9 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
     const int32_t chunk = (int32_t)(blockIdx.x % (unsigned)chunks);
     const int32_t split = (int32_t)(blockIdx.x / (unsigned)chunks);
     const int32_t nsg = (M + kSgExperts - 1) / kSgExperts;
-    const int32_t s0 = (int32_t)((int64_t)nsg * chunk / chunks);
-    const int32_t s1 = (int32_t)((int64_t)nsg * (chunk + 1) / chunks);
+    const int32_t nu = (nsg + unit - 1) / unit;
+    const int32_t s0 = (int32_t)((int64_t)nu * chunk / chunks) * unit;
+    const int32_t s1 = min((int32_t)((int64_t)nu * (chunk + 1) / chunks) * unit, nsg);
     const int nl = s1 - s0;
     if (hist)  // cleared for the histogram kernel (no memset: graph-safe)
         for (int64_t e = (int64_t)blockIdx.x * kSweepThreads + tid; e < M;
@@ -213,6 +216,7 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
             load_z(first);
             z_arrived();
         }
+        [[maybe_unused]] float last[TPW][3];        // coarse maxima of the three super-groups before
         for (int32_t s = s0 + we; s < s1; s += ew) {
             const uint16_t* sgrows = rows + (s - s0) * kSgExperts * C::STRIDE;
             bf16x8 a[RC];
@@ -307,7 +311,36 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
                     const uint32_t fo = ((uint32_t)s * (uint32_t)Tp + (uint32_t)t) * 8u + 4u * half;
                     *reinterpret_cast<u32x4*>(fine + fo) =
                         u32x4{pk[g][0], pk[g][1], pk[g][2], pk[g][3]};
-                    coarse[(uint32_t)t * (uint32_t)nCp + (uint32_t)(2 * s + half)] = cm[g];
+                }
+            }
+            // Coarse maxima: where a wave takes four super-groups of a multiple of four in turn, the two
+            // lane halves exchange theirs and each lane stores two of them.
+            const bool quad = C::QUADS && ew == 1 && s1 - (s & ~3) >= 4 && (s & ~3) >= s0;
+            if (!quad) {  // wave-uniform
+#pragma unroll
+                for (int g = 0; g < TPW; ++g) {
+                    const int32_t t = first + 32 * g + n;
+                    if (t < T) coarse[(uint32_t)t * (uint32_t)nCp + (uint32_t)(2 * s + half)] = cm[g];
+                }
+            } else if constexpr (C::QUADS) {
+                if ((s & 3) == 3) {
+#pragma unroll
+                    for (int g = 0; g < TPW; ++g) {
+                        const int32_t t = first + 32 * g + n;
+                        float q[4] = {last[g][0], last[g][1], last[g][2], cm[g]};
+                        lane_swap32(q[0], q[2]);
+                        lane_swap32(q[1], q[3]);
+                        if (t < T)
+                            *reinterpret_cast<f32x4*>(coarse + (uint32_t)t * (uint32_t)nCp +
+                                                      (uint32_t)(2 * (s - 3) + 4 * half)) =
+                                f32x4{q[0], q[2], q[1], q[3]};
+                    }
+                }
+#pragma unroll
+                for (int g = 0; g < TPW; ++g) {
+                    last[g][0] = last[g][1];
+                    last[g][1] = last[g][2];
+                    last[g][2] = cm[g];
                 }
             }
         }
@@ -1185,7 +1218,7 @@ constexpr size_t kMaximaLeast = (size_t)32 << 20;
 constexpr size_t kScratchAim = (size_t)240 << 20;     // z and maxima together, where the floor allows
 
 struct SweepGrid {
-    int32_t chunks, splits, ew;
+    int32_t chunks, splits, ew, unit;
 };
 
 // Work split of a sweep over T tokens: as few expert chunks as fit LDS while there are 256
@@ -1199,12 +1232,21 @@ SweepGrid sweep_grid(int32_t rc, int32_t T, int32_t nsg) {
     while (g.ew < kSweepWaves && (kSweepWaves / (2 * g.ew)) * wt >= T && 2 * g.ew <= sgs) g.ew *= 2;
     const int32_t btok = kSweepWaves / g.ew * wt;
     const int32_t ntb = (T + btok - 1) / btok;
-    int32_t C = (nsg + sgs - 1) / sgs;
     const int32_t want = (256 + ntb - 1) / ntb;
-    if (C < want) C = want < nsg ? want : nsg;
-    g.chunks = C;
-    int32_t S = 256 / C;
-    g.splits = S < 1 ? 1 : (S > ntb ? ntb : S);
+    // super-groups times token blocks of the largest workgroup, with chunks of whole units
+    auto split = [&](int32_t unit) {
+        const int32_t nu = (nsg + unit - 1) / unit;
+        int32_t C = (nu + sgs / unit - 1) / (sgs / unit);
+        if (C < want) C = want < nu ? want : nu;
+        const int32_t S = 256 / C;
+        g.unit = unit;
+        g.chunks = C;
+        g.splits = S < 1 ? 1 : (S > ntb ? ntb : S);
+        return (int64_t)unit * ((nu + C - 1) / C) * ((ntb + g.splits - 1) / g.splits);
+    };
+    // fours let the coarse maxima go out in whole pieces (see the kernel), if the split stays even
+    const int64_t ones = split(1);
+    if (g.ew == 1 && sgs % 4 == 0 && 16 * split(4) > 17 * ones) (void)split(1);
     return g;
 }
 
@@ -1214,7 +1256,7 @@ void launch_sweep(const SweepGrid& g, const BucketArgs& a, int32_t T, const uint
                   float2* cnorm, int32_t* hist, hipStream_t st) {
     hipLaunchKernelGGL((bucket_sweep_kernel<RC>), dim3((unsigned)g.chunks * (unsigned)g.splits),
                        dim3(kSweepThreads), 0, st, zh, a.R2t, T, a.r, a.M, g.chunks, g.splits, g.ew,
-                       Tp, nCp, fine, coarse, fnorm, cnorm, hist);
+                       g.unit, Tp, nCp, fine, coarse, fnorm, cnorm, hist);
 }
 
 template <int SEG, int NS, bool EXACT, int K, bool COOP>
@@ -1279,7 +1321,7 @@ bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t z_bytes
     p->off_fine = o;
     o += align256((size_t)nsg * p->slab * 32);
     p->off_coarse = o;
-    p->nCp = (2 * nsg + 3) / 4 * 4;
+    p->nCp = (2 * nsg + 7) / 8 * 8;  // rows of whole 32-byte pieces
     o += align256((size_t)p->slab * p->nCp * sizeof(float));
     p->off_fnorm = o;
     o += align256((size_t)nsg * 16 * sizeof(float2));

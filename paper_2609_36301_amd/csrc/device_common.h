@@ -187,6 +187,14 @@ __device__ __forceinline__ void lane_pair32(float x, float& a, float& b) {
     b = __builtin_bit_cast(float, (unsigned)r[1]);
 }
 
+// Swaps a of lanes 32 .. 63 with b of lanes 0 .. 31.
+__device__ __forceinline__ void lane_swap32(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a),
+                                                    __builtin_bit_cast(unsigned, b), false, false);
+    a = __builtin_bit_cast(float, (unsigned)r[0]);
+    b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
 // The same for lanes l and l ^ 16 (permlane16 swap: the odd rows of 16 lanes of the first operand
 // against the even rows of the second).
 __device__ __forceinline__ void lane_pair16(float x, float& a, float& b) {

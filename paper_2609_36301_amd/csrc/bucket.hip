@@ -1307,14 +1307,24 @@ bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t z_bytes
     size_t room = kScratchAim > z_bytes ? kScratchAim - z_bytes : 0;
     room = room > kMaximaBytes ? kMaximaBytes : (room < kMaximaLeast ? kMaximaLeast : room);
     int64_t slab = (int64_t)(room / token_bytes(nsg));
-    slab = slab >= 1024 ? slab / 1024 * 1024 : slab / 32 * 32;
+    // Whole rounds of the sweep, one token block for each of 256 workgroups, and what is left in a last
+    // slab, whose sweep is split finer (T 32768, r 16, M 262144: 4096 tokens each instead of even slabs of
+    // 4864, where some workgroups had a second block: 749 -> 644 us a call).
+    int32_t sgs, wt;
+    sweep_limits(sweep_rc(r), &sgs, &wt);
+    const int32_t chunks = (nsg + sgs - 1) / sgs;
+    const int64_t round = (int64_t)kSweepWaves * wt * (chunks < 256 ? 256 / chunks : 1);
+    const bool whole = slab >= round;
+    slab = whole ? slab / round * round : (slab >= 1024 ? slab / 1024 * 1024 : slab / 32 * 32);
     if (slab < 32) slab = 32;  // (M <= 2^24: 84 MB)
     const int64_t tp = (T + 31) / 32 * 32;
     if (slab > tp) slab = tp;
-    // even slabs: the last one is no smaller than the others by more than a block
-    const int64_t ns = (T + slab - 1) / slab;
-    const int64_t even = ((T + ns - 1) / ns + 255) / 256 * 256;
-    p->slab = even < slab ? even : slab;
+    if (!whole) {  // even slabs
+        const int64_t ns = (T + slab - 1) / slab;
+        const int64_t even = ((T + ns - 1) / ns + 255) / 256 * 256;
+        if (even < slab) slab = even;
+    }
+    p->slab = slab;
     size_t o = 0;
     p->off_cd = o;
     o += align256((size_t)T * sizeof(float));

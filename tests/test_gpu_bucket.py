@@ -46,13 +46,17 @@ def test_bucket_route_matches_resident_kernels_and_oracle(shape):
     assert rep.ok(), "%s: %s" % (shape, rep)
 
 
-def test_bucket_route_more_than_one_slab():
-    # 1.3 M experts: 208 MB hold the maxima of about 1000 tokens, so these take three slabs
-    T, h, r, M, k = 2900, 16, 16, 1300000, 8
+@pytest.mark.parametrize("T,h,r,M,k", [
+    # the maxima of a slab take up to 208 MB
+    (2900, 16, 16, 1300000, 8),    # about 1000 tokens: three even slabs, a workgroup per token
+    (11000, 16, 16, 200000, 8),    # 5120: two whole rounds of the sweep and 760, two tokens per wave and one each
+    (10300, 16, 32, 200003, 16),   # the same with a partial super-group
+])
+def test_bucket_route_more_than_one_slab(T, h, r, M, k):
     inp = make_inputs(T, h, r, M, seed=3)
-    got = route_lowrank(inp, k, tag="bucket slabs")
-    ref = route_lowrank(inp, k, m_chunks=8, tag="resident kernels")
-    for a, b in zip(got[:3], ref[:3]):
+    got = route_lowrank(inp, k, histogram=True, tag="bucket slabs")
+    ref = route_lowrank(inp, k, histogram=True, m_chunks=8, tag="resident kernels")
+    for a, b in zip(got, ref):
         assert np.array_equal(a, b)
 
 

@@ -398,9 +398,11 @@ constexpr int kSelThreads = 64 * kSelWaves;
 constexpr int kSelQ = 4;       // 16-byte pieces of the coarse row per lane and round
 constexpr int kSelList = 256;  // listed coarse or fine buckets per token
 constexpr int kSelFine = 4;    // fine values per lane and round
-// Up to here a workgroup takes one token: 128 tokens against 262144 experts 12.5 us, 33 with two tokens
-// per wave (16 workgroups for the whole chip).
-constexpr int32_t kSelCoopTokens = 1024;
+// Few tokens: a workgroup takes one, for a shorter chain of loads, against more work in all.  Whole calls,
+// one token per workgroup / two per wave: M 16384, r 64, k 8: 30.4 / 31.9 us at 512 tokens, 33.0 / 32.8 at
+// 1024, 36.6 / 34.5 at 1536; M 65536: 35.9 / 40.0 at 1024, 41.7 / 43.6, 48.7 / 45.4 at 2048; M 262144: 57 / 70,
+// 72 / 81, 90 / 98; r 16 and 128, k 16 and 32 cross at the same sizes or a little later.
+bool one_token_per_workgroup(int32_t T, int32_t M) { return T <= 1024 || (T <= 2048 && M >= 1 << 18); }
 
 // Lanes per token: 32, two tokens per wave (the bookkeeping is bound by issue, and two tokens share
 // it); the longest lists need the 64 lanes' maxima.  COOP: the four waves of a workgroup share one
@@ -1280,7 +1282,7 @@ void launch_select_k(const BucketArgs& a, int64_t t0, int32_t T, int32_t Tp, int
     constexpr bool X4 = EXACT && SEG >= 4;
 #define MORE_SELECT(S, X, K, COOP) \
     launch_select<S, NS, X, K, COOP>(a, t0, T, Tp, nCp, fine, coarse, fnorm, cnorm, st)
-    if (T <= kSelCoopTokens) {
+    if (one_token_per_workgroup(T, a.M)) {
         if (a.k <= 8)
             MORE_SELECT(S4, X4, 8, true);
         else if (a.k <= 16)

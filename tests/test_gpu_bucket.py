@@ -28,6 +28,8 @@ SHAPES = [
     (1100, 64, 32, 9000, 3, 0.5),
     (2050, 32, 16, 20001, 16, 0.25),
     (3000, 16, 64, 40000, 12, 0.5),
+    (2048, 16, 32, 270000, 4, 0.0),      # a workgroup per token up to 2048 of them
+    (2049, 16, 32, 270000, 4, 0.0),
     (3500, 16, 16, 33030, 8, 0.0),       # chunks of whole fours of super-groups, the last four not whole
     (3500, 16, 64, 21000, 8, 0.5),       # the same with one four per chunk
 ]

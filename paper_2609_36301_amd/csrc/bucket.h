@@ -34,9 +34,9 @@ struct BucketArgs {
     float *gate, *topval;  // topval nullable
 };
 
-// false when the shape is outside the route's limits.  z_bytes: what the caller keeps beside the
-// route's scratch; the slab is chosen so that both stay within 240 MB where 32 MB allow it.
-bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t z_bytes, BucketPlan* plan);
+// false when the shape is outside the route's limits.  beside: bytes that the caller keeps beside the
+// route's scratch; up to 208 MB of them, the slab is chosen so that both stay within 240 MB.
+bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t beside, BucketPlan* plan);
 hipError_t bucket_launch(const BucketPlan& plan, const BucketArgs& a, void* scratch,
                          hipStream_t stream);
 

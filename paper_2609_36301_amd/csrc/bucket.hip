@@ -1217,7 +1217,7 @@ size_t token_bytes(int32_t nsg) { return (size_t)nsg * 40 + 16; }
 
 constexpr size_t kMaximaBytes = (size_t)208 << 20;    // largest slab: within the 256 MB last-level cache
 constexpr size_t kMaximaLeast = (size_t)32 << 20;
-constexpr size_t kScratchAim = (size_t)240 << 20;     // z and maxima together, where the floor allows
+constexpr size_t kScratchAim = (size_t)240 << 20;     // with what is beside them, while that leaves kMaximaLeast
 
 struct SweepGrid {
     int32_t chunks, splits, ew, unit;
@@ -1301,13 +1301,13 @@ void launch_select_k(const BucketArgs& a, int64_t t0, int32_t T, int32_t Tp, int
 
 }  // namespace
 
-bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t z_bytes, BucketPlan* p) {
+bool bucket_make_plan(int64_t T, int32_t r, int32_t M, int32_t k, size_t beside, BucketPlan* p) {
     if (M < kBucketMinExperts || M > kBucketMaxExperts || r < 16 || r % 16 != 0 ||
         r > kBucketMaxRank || k > 32 || T < 1 || (int64_t)M * r >= ((int64_t)1 << 31))
         return false;
     const int32_t nsg = (M + kSgExperts - 1) / kSgExperts;
-    size_t room = kScratchAim > z_bytes ? kScratchAim - z_bytes : 0;
-    room = room > kMaximaBytes ? kMaximaBytes : (room < kMaximaLeast ? kMaximaLeast : room);
+    size_t room = kMaximaBytes;
+    if (beside + kMaximaLeast <= kScratchAim && room > kScratchAim - beside) room = kScratchAim - beside;
     int64_t slab = (int64_t)(room / token_bytes(nsg));
     // Whole rounds of the sweep, one token block for each of 256 workgroups, and what is left in a last
     // slab, whose sweep is split finer (T 32768, r 16, M 262144: 4096 tokens each instead of even slabs of

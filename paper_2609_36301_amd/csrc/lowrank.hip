@@ -33,6 +33,7 @@
 
 #include "device_common.h"
 #include "lowrank.h"
+#include "more.h"
 #include "route_device.h"
 
 namespace more {
@@ -1243,27 +1244,34 @@ bool lowrank_make_plan(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k, in
     off += route_ws * align256((size_t)T * q.cap * sizeof(int32_t));
     q.workspace_bytes = q.local ? 0 : off;
     // Bucket route: the library's choice wherever no fused route applies (one sweep over the expert
-    // axis instead of the resident route's two).  Its scratch follows z, z_hi and c.  The workspace
-    // is never smaller than what the lists of candidates would take (512 per token; 1024 with their
-    // bounds, and the entry slots of the workgroups, for many tokens and experts): the shapes
-    // that more_route_lowrank_noalloc takes and refuses are a contract of their own.
+    // axis instead of the resident route's two).  Its scratch follows z, z_hi and c.
+    // Where only slabs of fewer than 512 tokens fit its maxima (M above 2.5 million), the resident route's
+    // kernels load the expert rows less often: M 2^22, r 16, 1024 tokens 416 us against 558 in slabs of 320,
+    // M 2^24, 512 tokens 0.93 ms against 3.3; at M 2^21 786 against 778 in slabs of 640, 4096 tokens.
+    // (Unless their lists, and not the maxima, are too large for the entry point without a workspace.)
     q.off_bk = q.off_top;
-    q.bucket = m_chunks == 0 && !q.fused && bucket_make_plan(T, r, M, k, q.off_bk, &q.bk);
-    q.single_pass = q.bucket && T >= 4096 && M >= 32768;
-    if (q.bucket) {
-        size_t lists = off;
-        if (q.single_pass) {
-            int64_t C = (Mt + emax_tiles - 1) / emax_tiles;
-            const int64_t want = (256 + q.ntb - 1) / q.ntb;
-            if (C < want) C = want;
-            const int64_t S = C > 256 ? 1 : (256 / C < q.ntb ? 256 / C : q.ntb);
-            lists = align256((size_t)T * r * 4) + align256((size_t)T * r * 2) +
-                    3 * align256((size_t)T * 4) + align256((size_t)T * 8192) +
-                    (size_t)(C * S) * 278528;
-        }
+    if (m_chunks == 0 && !q.fused && bucket_make_plan(T, r, M, k, 0, &q.bk)) {
         const size_t need = q.off_bk + q.bk.bytes;
-        q.workspace_bytes = need > lists ? need : lists;
+        q.bucket = q.bk.slab >= 512 || q.bk.slab >= T ||
+                   (off > MORE_NOALLOC_SCRATCH_BYTES && need <= MORE_NOALLOC_SCRATCH_BYTES);
+        if (q.bucket) {
+            // never smaller than what the lists of candidates would take (512 per token; 1024 with their
+            // bounds, and the entry slots of the workgroups, for many tokens and experts)
+            size_t lists = off;
+            if (T >= 4096 && M >= 32768) {
+                int64_t C = (Mt + emax_tiles - 1) / emax_tiles;
+                const int64_t want = (256 + q.ntb - 1) / q.ntb;
+                if (C < want) C = want;
+                const int64_t S = C > 256 ? 1 : (256 / C < q.ntb ? 256 / C : q.ntb);
+                lists = align256((size_t)T * r * 4) + align256((size_t)T * r * 2) +
+                        3 * align256((size_t)T * 4) + align256((size_t)T * 8192) +
+                        (size_t)(C * S) * 278528;
+            }
+            q.workspace_bytes = need > lists ? need : lists;
+        }
     }
+    q.single_pass = m_chunks == 0 && !q.fused && T >= 4096 && M >= 32768 && M <= kBucketMaxExperts &&
+                    q.K <= 16 && h < (1 << 24);
     *p = q;
     return true;
 }

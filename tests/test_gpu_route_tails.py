@@ -94,3 +94,21 @@ def test_expert_offsets_at_long_ranks(T, r, M, k):
     rep = parity.evaluate(inp.x, inp.R1, inp.R2, k, idx, gate, topval,
                           rows=np.arange(0, T, 3, dtype=np.int64))
     assert rep.ok(), str(rep)
+
+
+def test_millions_of_experts():
+    """Where the maxima of few tokens fill a slab, the call takes the resident route's kernels: the
+    same result and no slower than asked for by a chunk count."""
+    torch = require_gpu()
+    T, h, r, M, k = 512, 64, 16, 1 << 23, 8
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x, R1t, R2t = (torch.randn(s, device="cuda", generator=gen).mul_(f).bfloat16()
+                   for s, f in (((T, h), 1.0), ((r, h), h ** -0.5), ((M, r), r ** -0.5)))
+    own = router.LowrankRouter(T, h, r, M, k, topval=True)
+    asked = router.LowrankRouter(T, h, r, M, k, topval=True, m_chunks=1024)
+    announce("route_lowrank T=%d h=%d r=%d M=%d k=%d" % (T, h, r, M, k))
+    a, b = own(x, R1t, R2t), asked(x, R1t, R2t)
+    assert torch.equal(a.idx, b.idx) and torch.equal(a.gate, b.gate) and torch.equal(a.topval, b.topval)
+    a, b = call_us(lambda: own(x, R1t, R2t)), call_us(lambda: asked(x, R1t, R2t))
+    print("[time] own choice %.1f us, resident kernels %.1f us" % (a, b), flush=True)
+    assert a < 1.25 * b

@@ -1254,21 +1254,7 @@ bool lowrank_make_plan(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k, in
         const size_t need = q.off_bk + q.bk.bytes;
         q.bucket = q.bk.slab >= 512 || q.bk.slab >= T ||
                    (off > MORE_NOALLOC_SCRATCH_BYTES && need <= MORE_NOALLOC_SCRATCH_BYTES);
-        if (q.bucket) {
-            // never smaller than what the lists of candidates would take (512 per token; 1024 with their
-            // bounds, and the entry slots of the workgroups, for many tokens and experts)
-            size_t lists = off;
-            if (T >= 4096 && M >= 32768) {
-                int64_t C = (Mt + emax_tiles - 1) / emax_tiles;
-                const int64_t want = (256 + q.ntb - 1) / q.ntb;
-                if (C < want) C = want;
-                const int64_t S = C > 256 ? 1 : (256 / C < q.ntb ? 256 / C : q.ntb);
-                lists = align256((size_t)T * r * 4) + align256((size_t)T * r * 2) +
-                        3 * align256((size_t)T * 4) + align256((size_t)T * 8192) +
-                        (size_t)(C * S) * 278528;
-            }
-            q.workspace_bytes = need > lists ? need : lists;
-        }
+        if (q.bucket) q.workspace_bytes = need;
     }
     q.single_pass = m_chunks == 0 && !q.fused && T >= 4096 && M >= 32768 && M <= kBucketMaxExperts &&
                     q.K <= 16 && h < (1 << 24);

@@ -100,32 +100,25 @@ bool wide_make_plan(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k, WideP
     o += wide_align((size_t)T * r * sizeof(uint16_t));
     q.off_cz = o;
     o += wide_align((size_t)T * sizeof(float));
-    const size_t head = o;
+    // The bucket route from kBucketMinExperts experts on: one sweep of the matrix cores instead of
+    // the three pieces' (T 16384, r 128, M 16384: 62 + 50 us against 410).
+    q.off_bk = o;
+    q.bucket = bucket_make_plan(T, r, M, k, o, &q.bk);
+    if (q.bucket) {
+        q.workspace_bytes = o + q.bk.bytes;
+        *out = q;
+        return true;
+    }
     // fused sweep: z_hi and the scale are not read again, the split takes their place
     q.off_zs = q.off_zhi;
-    o = q.off_zs + wide_align((size_t)T * 3 * r * sizeof(uint16_t));  // from off_zhi on
+    const size_t split = q.off_zs + wide_align((size_t)T * 3 * r * sizeof(uint16_t));
+    o = split > o ? split : o;
     q.stack = r % 64 != 0;
     q.off_w3 = o;
     if (q.stack) o += wide_align((size_t)M * 3 * r * sizeof(uint16_t));
     q.off_ff = o;
     o += wide_align(q.ff.workspace_bytes);
-    // what the fused sweep takes with z computed by blocks of 64, 32 and 16 columns
-    size_t zscr = 0;
-    for (int32_t j = 0; j < r;) {
-        const int32_t w = r - j >= 64 ? 64 : (r - j >= 32 ? 32 : 16);
-        const size_t s = zonly_workspace_bytes(T, h, w);
-        zscr = s > zscr ? s : zscr;
-        j += w;
-    }
-    const size_t blocks = o - wide_align(zpass_workspace_bytes(T, h, r)) + wide_align(zscr);
-    // The bucket route from kBucketMinExperts experts on: one sweep of the matrix cores instead of
-    // the three pieces' (T 16384, r 128, M 16384: 62 + 50 us against 410).  Below, its selection
-    // would read a large part of the experts' rows.  The workspace stays at least what the fused sweep
-    // took: the shapes that more_route_lowrank_noalloc takes and refuses are a contract of their own.
-    q.off_bk = head;
-    q.bucket = bucket_make_plan(T, r, M, k, head, &q.bk);
-    const size_t need = q.bucket ? head + q.bk.bytes : (o > head ? o : head);
-    q.workspace_bytes = need > blocks ? need : blocks;
+    q.workspace_bytes = o;
     *out = q;
     return true;
 }

@@ -176,21 +176,37 @@ def test_routes_for_the_paper_shapes(lib):
 
 
 def test_wide_route_workspace_sizes(lib):
-    # the wide route needs z, its three-piece split and (r not a multiple of 64) the stacked
-    # expert rows: more bytes for more tokens, for more experts when stacked, and at least z
+    # below 2048 experts the wide route needs z, its three-piece split and (r not a multiple of 64) the
+    # stacked expert rows: more bytes for more tokens, for more experts when stacked, and at least z
     n = ctypes.c_size_t(0)
     sizes = {}
-    for T, h, r, M, k in ((1000, 256, 128, 3000, 8), (2000, 256, 128, 3000, 8),
-                          (1000, 256, 80, 3000, 8), (1000, 256, 80, 6000, 8),
-                          (1000, 256, 64, 3000, 20)):
+    for T, h, r, M, k in ((1000, 256, 128, 1500, 8), (2000, 256, 128, 1500, 8),
+                          (1000, 256, 80, 1000, 8), (1000, 256, 80, 2000, 8),
+                          (1000, 256, 64, 1500, 20)):
         assert lib.more_route_lowrank_workspace_size(T, h, r, M, k, ctypes.byref(n)) == _lib.OK
         assert n.value >= T * r * 4 + T * 3 * r * 2
         sizes[(T, r, M, k)] = n.value
-    assert sizes[(2000, 128, 3000, 8)] > sizes[(1000, 128, 3000, 8)]
-    assert sizes[(1000, 80, 6000, 8)] - sizes[(1000, 80, 3000, 8)] >= 3000 * 3 * 80 * 2
+    assert sizes[(2000, 128, 1500, 8)] > sizes[(1000, 128, 1500, 8)]
+    assert sizes[(1000, 80, 2000, 8)] - sizes[(1000, 80, 1000, 8)] >= 1000 * 3 * 80 * 2
     # one byte short of the size query: refused before any launch
-    assert lowrank(lib, T=1000, h=256, r=128, M=3000, k=8, ws=FAKE,
-                   wsb=sizes[(1000, 128, 3000, 8)] - 1) == _lib.ERR_WORKSPACE
+    assert lowrank(lib, T=1000, h=256, r=128, M=1500, k=8, ws=FAKE,
+                   wsb=sizes[(1000, 128, 1500, 8)] - 1) == _lib.ERR_WORKSPACE
+
+
+def test_bucket_route_workspace_sizes(lib):
+    """z, z_hi and the two scales of every token, and the maxima of one slab of tokens (40 bytes per token and
+    256 experts, at most 208 MB): nothing else, whatever the number of tokens."""
+    n = ctypes.c_size_t(0)
+    for T, h, r, M, k in ((1000, 4096, 64, 20000, 8), (16384, 512, 32, 40000, 16), (131072, 512, 64, 32768, 8),
+                          (200, 64, 16, 1 << 24, 8), (3000, 256, 128, 2048, 8), (20000, 256, 240, 70000, 32),
+                          (900000, 64, 256, 4096, 8)):
+        assert lib.more_route_lowrank_workspace_size(T, h, r, M, k, ctypes.byref(n)) == _lib.OK
+        groups = (M + 255) // 256
+        z = T * (r * 6 + 8)
+        parts = T * r * 4 * min((h + 63) // 64, 256) if T < 32768 else 0  # partial sums of the z pass
+        maxima = min(T + 32, 208 * 2 ** 20 // (40 * groups)) * (40 * groups + 32)
+        assert z < n.value <= z + parts + maxima + 72 * groups + 4096 + 256 * 8, (T, h, r, M, k)
+        assert lowrank(lib, T=T, h=h, r=r, M=M, k=k, ws=FAKE, wsb=n.value - 1) == _lib.ERR_WORKSPACE
 
 
 def test_fullrank_validation(lib):

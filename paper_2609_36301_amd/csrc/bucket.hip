@@ -479,6 +479,11 @@ __device__ __forceinline__ float token_sort_desc(float x) {
     return x;
 }
 
+// Not infinite and not NaN, as an integer test: this file is compiled without NaNs in comparisons.
+__device__ __forceinline__ bool finite(float x) {
+    return (__builtin_bit_cast(uint32_t, x) & 0x7F800000u) != 0x7F800000u;
+}
+
 // The fine maxima are rounded to bf16: 2^-8 relative at most (and subnormals).
 __device__ __forceinline__ float slack(float x) { return fmaf(fabsf(x), 0x1.01p-8f, 0x1p-125f); }
 
@@ -557,9 +562,6 @@ __device__ __forceinline__ void select_long(const SelectArgs& a, LongLists<K>& m
         return __builtin_amdgcn_readfirstlane(b) +
                (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                               __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-    };
-    auto finite = [](float x) __attribute__((always_inline)) {
-        return (__builtin_bit_cast(uint32_t, x) & 0x7F800000u) != 0x7F800000u;
     };
     const float c = a.cz[t], d = a.cd[t];
     // infinite or NaN bounds say nothing: every expert is evaluated
@@ -1138,6 +1140,8 @@ __global__ __launch_bounds__(kSelThreads) void bucket_select_kernel(const Select
         nc = total(L3{}, nc);
         // fewer than k cannot happen (k experts reach theta); the test is a guard, not a path
         over = (over || nc < k) && !zero;
+        // nor do bounds that are infinite or NaN count for anything (d is, wherever z is)
+        over = over || !finite(d) || !finite(cr) || !(zero || finite(theta));
         nc = over ? 0 : nc;
         // rank of each candidate by counting; ranks below k write their output slot
         const int ncm = most(nc);

@@ -1,4 +1,5 @@
-"""Inputs that make the bucket route's lists long: padding tokens and experts that tie.
+"""Inputs that make the bucket route's lists long: padding tokens, experts that tie, expert offsets, values
+that are not finite; and expert sets too large for its slabs.
 Results stay exact, and a call does not stall: times are compared with the same shape on plain
 inputs, with bounds several times what is measured and a fraction of what sweeping all experts for
 such tokens takes."""
@@ -94,6 +95,25 @@ def test_expert_offsets_at_long_ranks(T, r, M, k):
     rep = parity.evaluate(inp.x, inp.R1, inp.R2, k, idx, gate, topval,
                           rows=np.arange(0, T, 3, dtype=np.int64))
     assert rep.ok(), str(rep)
+
+
+@pytest.mark.parametrize("T,r,M,k", [(60, 64, 6000, 8), (1500, 64, 6000, 16), (1300, 128, 2100, 32), (40, 240, 3000, 8)])
+def test_tokens_that_are_not_finite(T, r, M, k):
+    """An infinite, a NaN and an overflowing token get k distinct experts (which, is not specified) and leave the
+    others as they are."""
+    inp = make_inputs(T, 64, r, M, seed=r)
+    want = route_lowrank(inp, k, tag="finite")
+    inp.x[3, 5] = 0x7F80           # +inf
+    inp.x[T - 1, 0] = 0x7FC0       # NaN
+    inp.x[8] = 0x7F00              # 1.7e38 in every entry
+    bad = np.zeros(T, dtype=bool)
+    bad[[3, 8, T - 1]] = True
+    got = route_lowrank(inp, k, histogram=True, tag="not finite")
+    for a, b in zip(got[:3], want[:3]):
+        assert np.array_equal(a[~bad], b[~bad])
+    ids = np.sort(got[0][bad], axis=1)
+    assert ids.min() >= 0 and ids.max() < M and np.all(ids[:, 1:] != ids[:, :-1])
+    assert got[3].sum() == T * k
 
 
 def test_millions_of_experts():

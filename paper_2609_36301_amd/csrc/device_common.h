@@ -46,26 +46,8 @@ __device__ __forceinline__ constexpr int acc_row(int e, int half) {
     return 8 * (e >> 2) + 4 * half + (e & 3);
 }
 
-// fp32 -> bfloat16 bits, round to nearest even (finite inputs).
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) {
     return __builtin_bit_cast(float, b << 16);
-}
-
-// Split eight fp32 values into bf16 hi = bf16(z) and lo = bf16(z - hi), both rounded to
-// nearest even (v_cvt_pk_bf16_f32).  z - hi is exact in fp32, so hi + lo carries about 16
-// significant bits of z.
-__device__ __forceinline__ void split_hi_lo(const float (&z)[8], bf16x8& hi, bf16x8& lo) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const __bf16 h = (__bf16)z[q];
-        hi[q] = h;
-        lo[q] = (__bf16)(z[q] - (float)h);
-    }
 }
 
 // ---------------------------------------------------------------- top-K lists
@@ -156,8 +138,8 @@ __device__ __forceinline__ void list_merge(float (&av)[K], int32_t (&ai)[K], con
 // ---------------------------------------------------------------- cross-lane moves
 // The value of x held by lane (lane ^ M).  M = 1 and 2 are DPP quad permutations, M = 4 a
 // half-row mirror followed by a quad reversal (lane i of an 8-lane group reads 7 - (i ^ 3) =
-// i ^ 4), M = 8 a rotation of the 16-lane row by half; these stay in the VALU instead of going through the LDS crossbar of a general
-// shuffle.  Other M use __shfl_xor.
+// i ^ 4), M = 8 a rotation of the 16-lane row by half; these stay in the VALU instead of going
+// through the LDS crossbar of a general shuffle.  Other M use __shfl_xor.
 template <int M, typename T>
 __device__ __forceinline__ T lane_xor(T x) {
     static_assert(sizeof(T) == 4, "32-bit values only");
@@ -232,32 +214,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_s_waitcnt((15) | (3 << 14) | (7 << 4));
     __builtin_amdgcn_wave_barrier();
     asm volatile("" ::: "memory");
-}
-
-// x sorted descending across the 64 lanes of the wave (lane 0 the largest): bitonic network
-// of 21 compare-exchange stages, partners by lane_xor.
-__device__ __forceinline__ float wave_sort_desc(float x, int lane) {
-#pragma unroll
-    for (int size = 2; size <= 64; size <<= 1) {
-#pragma unroll
-        for (int d = size >> 1; d >= 1; d >>= 1) {
-            float y;
-            switch (d) {
-                case 1: y = lane_xor<1>(x); break;
-                case 2: y = lane_xor<2>(x); break;
-                case 4: y = lane_xor<4>(x); break;
-                case 8: y = lane_xor<8>(x); break;
-                case 16: y = lane_xor<16>(x); break;
-                default: y = lane_xor<32>(x); break;
-            }
-            // within blocks of `size`, descending where (lane & size) == 0 (the last stage
-            // has size 64: all descending); the lower lane of a pair keeps the larger value
-            const bool desc = (lane & size) == 0 || size == 64;
-            const bool lower = (lane & d) == 0;
-            x = (lower == desc) ? fmaxf(x, y) : fminf(x, y);
-        }
-    }
-    return x;
 }
 
 // softmax over the first k entries of a sorted list, then store idx / gate / topval row.

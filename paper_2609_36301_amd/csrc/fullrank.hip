@@ -34,6 +34,32 @@ namespace more {
 // counted against the others.  Rows with more than 128 such logits (ties) use the list path.
 constexpr int kRowsCap = 128;  // candidates per row on the threshold path
 
+// x sorted descending across the 64 lanes of the wave (lane 0 the largest): bitonic network
+// of 21 compare-exchange stages, partners by lane_xor.
+__device__ __forceinline__ float wave_sort_desc(float x, int lane) {
+#pragma unroll
+    for (int size = 2; size <= 64; size <<= 1) {
+#pragma unroll
+        for (int d = size >> 1; d >= 1; d >>= 1) {
+            float y;
+            switch (d) {
+                case 1: y = lane_xor<1>(x); break;
+                case 2: y = lane_xor<2>(x); break;
+                case 4: y = lane_xor<4>(x); break;
+                case 8: y = lane_xor<8>(x); break;
+                case 16: y = lane_xor<16>(x); break;
+                default: y = lane_xor<32>(x); break;
+            }
+            // within blocks of `size`, descending where (lane & size) == 0 (the last stage
+            // has size 64: all descending); the lower lane of a pair keeps the larger value
+            const bool desc = (lane & size) == 0 || size == 64;
+            const bool lower = (lane & d) == 0;
+            x = (lower == desc) ? fmaxf(x, y) : fminf(x, y);
+        }
+    }
+    return x;
+}
+
 template <int K, bool BF16, int NPL>
 __global__ __launch_bounds__(256) void rows_topk_short_kernel(const void* __restrict__ logits,
                                                               int32_t T, int32_t M, int32_t k,

@@ -1140,8 +1140,7 @@ __global__ __launch_bounds__(kRouteThreads, 2) void fused_local_kernel(
     }
     fused_phases<RC, K, true>(
         [&](const f32x16(&cin)[TPW], auto&& body) __attribute__((always_inline)) {
-            sweep_regs<RC, K, TPW, NTW, false>(areg, nullptr, nt, rot, e00, M, half, tg.zhi, cin,
-                                               body);
+            sweep_regs<RC, K, TPW, NTW>(areg, nt, rot, e00, tg.zhi, cin, body);
         },
         tg, wave_norm, sh, [&](int j) __attribute__((always_inline)) { return zs + j * ZSP; }, R2t, T,
         M, k, tok0, idx, gate, topval);

@@ -471,19 +471,17 @@ __device__ __forceinline__ void sweep_cin(const Src& src, int nt, int half,
 
 // The same sweep over tiles whose A operands are held in registers (slot J < nt <= NTW holds
 // tile (J + rot) mod nt, loaded by the caller).  The accumulator of token group g starts from
-// cin[g] (the MFMA adds it for free); with NQ the norms come from LDS (gn + 8 t + 4 half),
-// otherwise nq is zero.  Slots are fully unrolled, so register indices are compile-time
+// cin[g] (the MFMA adds it for free), which holds the norm bounds; the body's own are zero.  Slots are fully unrolled, so register indices are compile-time
 // constants; the bucket of slot J is J mod U.
-template <int RC, int K, int TPW, int NTW, bool NQ, typename Body>
-__device__ __forceinline__ void sweep_regs(const bf16x8 (&a)[NTW][RC], const float* gn, int nt,
-                                           int rot, int32_t e00, int32_t M, int half,
+template <int RC, int K, int TPW, int NTW, typename Body>
+__device__ __forceinline__ void sweep_regs(const bf16x8 (&a)[NTW][RC], int nt, int rot, int32_t e00,
                                            const bf16x8 (&zhi)[TPW][RC],
                                            const f32x16 (&cin)[TPW], Body&& body) {
     using C = RouteCfg<RC, K>;
     constexpr int H = TPW / 2;
     constexpr int U = C::U;
     f32x16 acc[TPW];
-    f32x4 nq[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+    const f32x4 nq{0.0f, 0.0f, 0.0f, 0.0f};
     auto mfmas = [&](auto jj, auto hh) __attribute__((always_inline)) {
         constexpr int J = decltype(jj)::value;
         constexpr int G0 = decltype(hh)::value * H;
@@ -501,7 +499,7 @@ __device__ __forceinline__ void sweep_regs(const bf16x8 (&a)[NTW][RC], const flo
             constexpr int G = G0 + decltype(gg)::value;
             const int tj = J + rot < nt ? J + rot : J + rot - nt;  // the slot's tile
             body(std::integral_constant<int, G>{}, acc[G], e00 + tj * 32,
-                 std::integral_constant<int, J % U>{}, nq[J & 1]);
+                 std::integral_constant<int, J % U>{}, nq);
         });
     };
     using I0 = std::integral_constant<int, 0>;
@@ -509,10 +507,6 @@ __device__ __forceinline__ void sweep_regs(const bf16x8 (&a)[NTW][RC], const flo
     unroll<NTW>([&](auto jj) __attribute__((always_inline)) {
         constexpr int J = decltype(jj)::value;
         if (J < nt) {  // wave-uniform
-            if constexpr (NQ) {
-                const int tj = J + rot < nt ? J + rot : J + rot - nt;
-                nq[J & 1] = *reinterpret_cast<const f32x4*>(gn + tj * 8 + 4 * half);
-            }
             mfmas(jj, I0{});
             if constexpr (J > 0) finish(std::integral_constant<int, J - 1>{}, I1{});
             mfmas(jj, I1{});
@@ -678,13 +672,8 @@ __device__ __forceinline__ float exact_logit(const ZRow& zr, const uint16_t* __r
 //  - more (an overflowed list): the whole workgroup sweeps all M experts for the token.
 // Either way the softmax adds exp(l - l_max) in rank order, so every path gives the same bits.
 // Must be reached by every thread of the workgroup.
-// on_select(e) is called once for every selected expert (for a histogram), by some thread.
-struct NoSelectHook {
-    __device__ __forceinline__ void operator()(int32_t) const {}
-};
-
 template <int RC, int K, int NTHREADS, int RCAP, typename ZRowOf, typename CountOf,
-          typename CandOf, typename OnSelect = NoSelectHook>
+          typename CandOf>
 __device__ __forceinline__ void finalize_tokens(ZRowOf&& zrow_of,
                                                 const uint16_t* __restrict__ R2t, int32_t T,
                                                 int32_t M, int32_t k, int64_t tok0, int32_t cap,
@@ -692,8 +681,7 @@ __device__ __forceinline__ void finalize_tokens(ZRowOf&& zrow_of,
                                                 float* lv, int32_t* le,
                                                 int32_t* __restrict__ idx,
                                                 float* __restrict__ gate,
-                                                float* __restrict__ topval,
-                                                OnSelect&& on_select = OnSelect{}) {
+                                                float* __restrict__ topval) {
     constexpr int R = 16 * RC;
     constexpr int NTOK = NTHREADS / 8, NW = NTHREADS / 64;
     __shared__ int32_t over_flag[NTOK];
@@ -760,11 +748,6 @@ __device__ __forceinline__ void finalize_tokens(ZRowOf&& zrow_of,
         list_merge_xor<2, K>(v, ix);
         list_merge_xor<4, K>(v, ix);
         if (ok && sub == 0 && !exact_sweep) store_selection<K>(v, ix, k, tok, idx, gate, topval);
-        if (ok && !exact_sweep) {
-#pragma unroll
-            for (int q = 0; q < K; ++q)
-                if (q < k && (q & 7) == sub) on_select(ix[q]);
-        }
     }
     if constexpr (RCAP > 0) {
     static_assert(RCAP % 8 == 0, "rank path: chunks of 8 entries");
@@ -819,7 +802,6 @@ __device__ __forceinline__ void finalize_tokens(ZRowOf&& zrow_of,
                     idx[tok * k + rank] = e;
                     if (topval) topval[tok * k + rank] = l;
                     ex[j][rank] = expf(l - lmax);
-                    on_select(e);
                 }
             }
         }
@@ -873,7 +855,6 @@ __device__ __forceinline__ void finalize_tokens(ZRowOf&& zrow_of,
                 list_merge<K>(v, ix, bv, bi);
             }
             store_selection<K>(v, ix, k, t, idx, gate, topval);
-            for (int q = 0; q < k; ++q) on_select(ix[q]);
         }
         __syncthreads();
     }

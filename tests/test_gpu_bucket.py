@@ -94,6 +94,10 @@ WIDE = [
     (1050, 32, 256, 2304, 32, 0.0),
     (1030, 64, 16, 20000, 24, 0.0),
     (90, 64, 32, 7000, 32, 0.5),
+    (1030, 64, 192, 3000, 16, 0.5),
+    (1026, 32, 256, 2304, 32, 0.5),
+    (33, 64, 256, 5000, 32, 0.5),
+    (1030, 64, 128, 6000, 17, 0.5),
 ]
 
 

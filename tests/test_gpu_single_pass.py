@@ -1,13 +1,11 @@
-"""GPU parity of the single-pass route (the library's choice for at least 4096 tokens and at least
-32768 experts): oracle parity on every token, agreement with the resident route (m_chunks = 8,
-two full sweeps) and the histogram.  The single-pass route computes z = x R1 in its own
-summation order, so its fp32 logits can differ from the resident route's in the last bits:
-selections agree wherever the k-th and (k+1)-th logits are not within rounding of each other.
+"""GPU parity of the route reported as single-pass (the library's choice for at least 4096 tokens and at
+least 32768 experts; the bucket route's sweep and selection): oracle parity on every token, bitwise
+agreement with the resident route's kernels (m_chunks = 8: another screening, the same z and the same
+exact sums) and the histogram.
 
 Shapes cover every rank width (r = 16, 32, 64), every top-K list size of the kernels (k = 1, 2,
-3, 5, 16), ragged token counts (a partial 512-token block and a partial 64-token group) and
-ragged expert counts (a partial last tile), plus the degenerate and tied cases that send tokens
-down the finalize kernel's exact sweep.
+3, 5, 16), ragged token counts (a partial block of the sweep) and ragged expert counts (a partial last
+tile), plus zero tokens and tied experts.
 """
 import numpy as np
 import pytest
@@ -44,20 +42,16 @@ def test_single_pass_parity_and_resident_route_agreement(shape):
     idx, gate, topval, counts = route_lowrank(inp, k, histogram=True, tag="single-pass")
     _check(inp, k, idx, gate, topval, str(shape))
     assert np.array_equal(counts, oracle.histogram(idx, M).astype(np.int32))
-    _agree_with_resident(inp, k, idx, topval)
+    _agree_with_resident(inp, k, idx, gate, topval)
 
 
-def _agree_with_resident(inp, k, idx, topval):
-    ref_idx, _, ref_tv, _ = route_lowrank(inp, k, m_chunks=8, tag="resident")
-    same = np.all(idx == ref_idx, axis=1)
-    # differing rows: a near tie at the k-th logit (both selections then pass the band check)
-    assert same.mean() > 0.999, same.mean()
-    assert np.allclose(topval[same], ref_tv[same], rtol=1e-5, atol=1e-6)
+def _agree_with_resident(inp, k, idx, gate, topval):
+    for a, b in zip((idx, gate, topval), route_lowrank(inp, k, m_chunks=8, tag="resident")):
+        assert np.array_equal(a, b)
 
 
-def test_single_pass_zero_tokens_take_the_exact_sweep():
-    """Zero-vector tokens tie every expert at logit 0: their record lists overflow and the
-    finalize kernel sweeps all experts exactly.  Expected: experts 0..k-1, gates 1/k, logits 0."""
+def test_single_pass_zero_tokens():
+    """Zero-vector tokens tie every expert at logit 0.  Expected: experts 0..k-1, gates 1/k, logits 0."""
     T, h, r, M, k = 4096, 256, 32, 33000, 8
     inp = make_inputs(T, h, r, M, seed=5)
     zero_rows = [0, 63, 64, 511, 512, 2047, 4095]
@@ -81,4 +75,4 @@ def test_single_pass_exact_ties_resolve_to_lower_expert():
     rep = parity.compare_with(orc, inp.x, inp.R1, inp.R2, k, idx, gate, topval)
     print("[parity] single-pass ties %s" % rep, flush=True)
     assert rep.ok(), str(rep)
-    _agree_with_resident(inp, k, idx, topval)
+    _agree_with_resident(inp, k, idx, gate, topval)

@@ -304,8 +304,9 @@ __global__ __launch_bounds__(256) void zreduce_kernel(const float* __restrict__ 
     for (int m = 1; m < r; m <<= 1) {
         hi2 += __shfl_xor(hi2, m, kWave);
         lo2 += __shfl_xor(lo2, m, kWave);
-        lo1 += __shfl_xor(lo1, m, kWave);
     }
+    if (d_out)
+        for (int m = 1; m < r; m <<= 1) lo1 += __shfl_xor(lo1, m, kWave);
     if (ok) {
         z[i] = s;
         zhi[i] = __builtin_bit_cast(uint16_t, hb);
@@ -352,8 +353,9 @@ __global__ __launch_bounds__(256) void zreduce_wide_kernel(const float* __restri
     for (int m = 1; m < 64; m <<= 1) {
         hi2 += __shfl_xor(hi2, m, kWave);
         lo2 += __shfl_xor(lo2, m, kWave);
-        lo1 += __shfl_xor(lo1, m, kWave);
     }
+    if (d_out)
+        for (int m = 1; m < 64; m <<= 1) lo1 += __shfl_xor(lo1, m, kWave);
     if (lane == 0) {
         cz[t] = screen_scale(lo2, hi2, r);
         if (d_out) d_out[t] = mean_scale(lo1, hi2, r);

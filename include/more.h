@@ -55,8 +55,12 @@
  *    are then evaluated exactly in fp32 (fp32 z times the bfloat16 expert rows).  The paper's
  *    kernel instead narrows z to one bfloat16 for the whole contraction.  Shapes outside the
  *    register-tiled routes (r not in {16, 32, 64}, or k > 16) take the wide route
- *    (MORE_ROUTE_WIDE): fp32 z split exactly into three bfloat16 pieces and one fused sweep of
- *    the matrix cores over the 3r-wide pair, i.e. the same fp32 logits up to summation order.
+ *    (MORE_ROUTE_WIDE): from 2048 experts on the same screening and exact evaluation, the fp32
+ *    sums taken in pieces of eight; below, fp32 z split exactly into three bfloat16 pieces and one
+ *    fused sweep of the matrix cores over the 3r-wide pair.  Either way the same fp32 logits up to
+ *    summation order.
+ *  - Inputs are finite.  What a token gets whose z is not (an infinity or NaN in its row, or an
+ *    overflow) is not specified.
  */
 #ifndef MORE_H
 #define MORE_H
@@ -111,8 +115,8 @@ more_status more_route_lowrank_workspace_size(int64_t T, int32_t h, int32_t r, i
  * bitwise identical results, and so does the fused route that reads the z pass (r M <= 2^18).
  * The one-launch fused route (r M <= 2^17 with K <= 8, and M <= 1024 at r = 64) computes z
  * inside the routing workgroup, summing the h axis in another order: its logits can differ from
- * the others' in the last bits (selections only where logits tie to rounding); so can those of
- * the routes that m_chunks = 0 picks for larger expert sets.  This entry
+ * the others' in the last bits (selections only where logits tie to rounding).  The routes that
+ * m_chunks = 0 picks for larger expert sets return the bits of m_chunks >= 1.  This entry
  * point exists for tuning and for tests of these properties.  The wide route ignores m_chunks
  * (any valid value gives the same result).  Its workspace size comes from
  * more_route_lowrank_workspace_size_ex with the same m_chunks (0 bytes for the one-launch
@@ -131,19 +135,22 @@ more_status more_route_lowrank_workspace_size_ex(int64_t T, int32_t h, int32_t r
  * shape with a route that no m_chunks >= 1 selects: a fused route (expert sets with
  * r * M <= 2^18 and M <= 16384: one workgroup per 64 tokens sweeps all experts) or the
  * single-pass route (T >= 4096 and M >= 32768) or the wide route.  (With m_chunks = 0 both larger
- * routes make one screening sweep that keeps bucket maxima; the chunk count is what a call with
- * an explicit m_chunks would take.) */
+ * routes make one screening sweep that keeps bucket maxima, up to about 2.5 million experts; the
+ * chunk count is what a call with an explicit m_chunks would take.) */
 more_status more_route_lowrank_plan(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k,
                                     int32_t* m_chunks);
 
 /* The route more_route_lowrank takes for this shape (written to *route, host): one of the
  * MORE_ROUTE_* codes below.  Routes differ in speed and in the summation order of z = x R1 (see
  * more_route_lowrank_ex); every route returns the exact top k of its own fp32 logits. */
-#define MORE_ROUTE_RESIDENT 0    /* z pass; one sweep that keeps bucket maxima, selection       */
+#define MORE_ROUTE_RESIDENT 0    /* z pass; one sweep that keeps bucket maxima, selection
+                                    (M above about 2.5 million and more than a few hundred tokens:
+                                    screen and collect sweeps, exact top k of the candidates)  */
 #define MORE_ROUTE_FUSED 1       /* z pass; one fused kernel per 64 tokens over all experts     */
 #define MORE_ROUTE_FUSED_LOCAL 2 /* one launch: the fused kernel also computes z                */
 #define MORE_ROUTE_SINGLE_PASS 3 /* the same, for T >= 4096 and M >= 32768                      */
-#define MORE_ROUTE_WIDE 4        /* z per rank block; exact 3-piece split; fused 3r-wide sweep */
+#define MORE_ROUTE_WIDE 4        /* z pass over all rank columns; M >= 2048: sweep and selection
+                                    as above; below: exact 3-piece split, fused 3r-wide sweep   */
 more_status more_route_lowrank_route(int64_t T, int32_t h, int32_t r, int32_t M, int32_t k,
                                      int32_t* route);
 

@@ -9,6 +9,10 @@
 namespace more {
 
 constexpr int32_t kBucketMaxRank = 256;
+// Below, each token's selection reads a large part of all rows.  T 16384, r 128, against the three-piece
+// sweep of the wide route: k 8 83 us and 115 at M 2048, 81 and 103 at 1536, 78 and 90 at 1024, 75 and 73 at
+// 512; k 32 147 and 243 at 1024, 263 and 179 at 512: the crossing lies between 512 and 1024, and this line
+// is on the safe side of it.
 constexpr int32_t kBucketMinExperts = 2048;
 constexpr int32_t kBucketMaxExperts = 1 << 24;
 

@@ -99,9 +99,10 @@ __device__ __forceinline__ float max16(const f32x16& a) {
 // super-groups s0 + i, s0 + i + ew, ...): ew > 1 keeps the waves busy when there are few tokens.
 // Each A operand read from LDS feeds TPW MFMAs.  Per tile and token group the epilogue is eight
 // v_max3 and half a pack, against RC MFMAs: the sweep is bound by the matrix cores.
-// Measured (T 32768, r 64, M 16384): 62 us, 1.1 PFLOP/s, of which the stores of the maxima take 9 and
+// Measured (T 32768, r 64, M 16384): 61 us, 1.1 PFLOP/s, of which the stores of the maxima take 9 and
 // the first loads of the rows 5; the two sweeps of the resident route (screen and collect) that
-// it replaces took 66 + 88 us.
+// it replaces took 66 + 88 us.  At r 16 the stores bound it: 1024 tokens, M 2^20 58 us, 168 MB of maxima
+// (88 with the coarse ones going out 4 bytes at a time).
 template <int RC>
 __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
     const uint16_t* __restrict__ zh, const uint16_t* __restrict__ R2t, int32_t T, int32_t r,

@@ -5,7 +5,8 @@
 //   bucket           zpass (z = x R1, fp32) [+ zreduce when the h axis is split over workgroups], then
 //                    the sweep and select kernels of bucket.hip (reported as the expert-resident
 //                    route, or as the single-pass route for many tokens and experts);
-//   expert-resident  an explicit chunk count (and fewer than 2048 experts outside the fused routes):
+//   expert-resident  an explicit chunk count, products M r of 2^31 and more, more than 2^24 experts, and
+//                    expert sets of which the bucket route could only take a few hundred tokens at a time:
 //                    zpass (with the group norms of R2t's rows unless the screen kernel takes
 //                    them), then screen, threshold, collect and finalize kernels; screen and
 //                    collect workgroups hold one chunk of the expert axis in LDS;

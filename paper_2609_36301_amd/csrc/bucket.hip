@@ -48,6 +48,7 @@ constexpr int kSgTiles = 8;                  // MFMA tiles of a super-group
 constexpr int kSgExperts = 32 * kSgTiles;    // 256
 constexpr int kSweepWaves = 8;
 constexpr int kSweepThreads = 64 * kSweepWaves;
+static_assert(kSweepThreads == 2 * kSgExperts, "the norm bounds take two super-groups at a time");
 constexpr int kSweepLds = 140 * 1024;        // expert rows of a workgroup
 
 // Layout of the expert rows in LDS.  Powers of two keep the unpadded XOR swizzle of RouteCfg; other
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
     using C = SweepCfg<RC>;
     constexpr int TPW = C::TPW, H = C::HALVES ? TPW / 2 : TPW;
     __shared__ __attribute__((aligned(16))) uint16_t rows[C::SGS * kSgExperts * C::STRIDE];
-    __shared__ float2 nred[16];
+    __shared__ float2 nred[2][16];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -347,11 +348,12 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
         }
     }
 
-    // ---- norm bounds of the buckets; the splits share the chunk's super-groups.
+    // ---- norm bounds of the buckets, two super-groups at a time; the splits share the chunk's.
     const float rinv = 1.0f / (float)r;
-    for (int i = split; i < nl; i += splits) {      // workgroup-uniform
-        if (tid < kSgExperts) {
-            const int e = i * kSgExperts + tid;
+    const int part = tid / kSgExperts, row = tid % kSgExperts;  // (part is wave-uniform)
+    for (int i0 = 2 * split; i0 < nl; i0 += 2 * splits) {       // workgroup-uniform
+        if (i0 + part < nl) {
+            const int e = (i0 + part) * kSgExperts + row;
             float ss = 0.0f, su = 0.0f;
 #pragma unroll
             for (int sg = 0; sg < C::SPR; ++sg) {
@@ -374,20 +376,21 @@ __global__ __launch_bounds__(kSweepThreads, 2) void bucket_sweep_kernel(
             over(std::integral_constant<int, 8>{});
             over(std::integral_constant<int, 16>{});
             if ((lane & 27) == 0) {
-                const int f = ((tid >> 2) & 1) * kSgTiles + (tid >> 5);
-                fnorm[(s0 + i) * 16 + f] = nb;
-                nred[f] = nb;
+                const int f = ((row >> 2) & 1) * kSgTiles + (row >> 5);
+                fnorm[(s0 + i0 + part) * 16 + f] = nb;
+                nred[part][f] = nb;
             }
         }
         __syncthreads();
-        if (tid < 2) {
-            float2 m = nred[tid * kSgTiles];
+        if (tid < 4 && i0 + (tid >> 1) < nl) {
+            const float2* half_nb = &nred[tid >> 1][(tid & 1) * kSgTiles];
+            float2 m = half_nb[0];
 #pragma unroll
             for (int q = 1; q < kSgTiles; ++q) {
-                m.x = fmaxf(m.x, nred[tid * kSgTiles + q].x);
-                m.y = fmaxf(m.y, nred[tid * kSgTiles + q].y);
+                m.x = fmaxf(m.x, half_nb[q].x);
+                m.y = fmaxf(m.y, half_nb[q].y);
             }
-            cnorm[2 * (s0 + i) + tid] = m;
+            cnorm[2 * (s0 + i0) + tid] = m;
         }
         __syncthreads();
     }

@@ -273,6 +273,21 @@ __global__ __launch_bounds__(256) void zpass_kernel(const uint16_t* __restrict__
     }
 }
 
+// The three sums over groups of n = 16, 32 or 64 lanes.
+__device__ __forceinline__ void token_sums(float& a, float& b, float& c, int n) {
+    auto add = [&](auto m) __attribute__((always_inline)) {
+        a += lane_xor<decltype(m)::value>(a);
+        b += lane_xor<decltype(m)::value>(b);
+        c += lane_xor<decltype(m)::value>(c);
+    };
+    add(std::integral_constant<int, 1>{});
+    add(std::integral_constant<int, 2>{});
+    add(std::integral_constant<int, 4>{});
+    add(std::integral_constant<int, 8>{});
+    if (n > 16) add(std::integral_constant<int, 16>{});
+    if (n > 32) add(std::integral_constant<int, 32>{});
+}
+
 // Sums the h-split partials of z (per element, splits in increasing order), then writes z,
 // z_hi = bf16(z) and the token's error scales c and d (d_out nullable).  256 threads = 256 / r tokens, one thread per
 // element; the r threads of a token are consecutive lanes of one wave.
@@ -302,12 +317,7 @@ __global__ __launch_bounds__(256) void zreduce_kernel(const float* __restrict__ 
     const float hf = (float)hb;
     const float lf = s - hf;
     float hi2 = hf * hf, lo2 = lf * lf, lo1 = lf;
-    for (int m = 1; m < r; m <<= 1) {
-        hi2 += __shfl_xor(hi2, m, kWave);
-        lo2 += __shfl_xor(lo2, m, kWave);
-    }
-    if (d_out)
-        for (int m = 1; m < r; m <<= 1) lo1 += __shfl_xor(lo1, m, kWave);
+    token_sums(hi2, lo2, lo1, r);
     if (ok) {
         z[i] = s;
         zhi[i] = __builtin_bit_cast(uint16_t, hb);
@@ -351,12 +361,7 @@ __global__ __launch_bounds__(256) void zreduce_wide_kernel(const float* __restri
         z[i] = s;
         zhi[i] = __builtin_bit_cast(uint16_t, hb);
     }
-    for (int m = 1; m < 64; m <<= 1) {
-        hi2 += __shfl_xor(hi2, m, kWave);
-        lo2 += __shfl_xor(lo2, m, kWave);
-    }
-    if (d_out)
-        for (int m = 1; m < 64; m <<= 1) lo1 += __shfl_xor(lo1, m, kWave);
+    token_sums(hi2, lo2, lo1, 64);
     if (lane == 0) {
         cz[t] = screen_scale(lo2, hi2, r);
         if (d_out) d_out[t] = mean_scale(lo1, hi2, r);

@@ -2,7 +2,8 @@
 multiple of 16 up to 256, the paper's rank sweeps in Section "Routing expressivity") and
 17 <= k <= 32, against the fp64 oracle under the rules of oracle/parity.py.
 
-Shapes span every rank-block mix of the z pass (64-, 32- and 16-wide blocks), ragged token and
+Shapes span the rank widths of the z pass (tiles of 32, 64, 128 and 256 rank rows, full and padded),
+both sides of the 2048 experts from which the bucket sweep and selection follow it, ragged token and
 expert counts, k at both ends of the list lengths and one token; a larger shape is checked on
 sampled tokens.  The route's own properties: the plain entry point and the _ex one with any
 m_chunks give identical bits, repeated calls are bitwise reproducible, the histogram matches
@@ -32,15 +33,15 @@ def _check(inp, k, idx, gate, topval, rows=None, label=""):
 
 SHAPES = [
     # T, h, r, M, k
-    (1, 32, 240, 7, 1),          # one token; blocks 64+64+64+32+16
+    (1, 32, 240, 7, 1),          # one token; r just below the largest tile
     (64, 64, 16, 33, 32),        # k = 32 with M = 33 at the smallest rank
     (201, 64, 128, 301, 32),     # r = 128 with the longest list
-    (257, 96, 80, 777, 17),      # blocks 64+16, k just past the register-tiled routes
-    (513, 256, 48, 1000, 4),     # blocks 32+16
-    (300, 512, 256, 2049, 8),    # r = 256: four 64-wide blocks, ragged expert tile
-    (1000, 512, 112, 2048, 10),  # blocks 64+32+16, k = 10 (the paper's largest frontier k)
+    (257, 96, 80, 777, 17),      # k just past the register-tiled routes
+    (513, 256, 48, 1000, 4),     # r padded to 64
+    (300, 512, 256, 2049, 8),    # r = 256, ragged expert tile; bucket sweep
+    (1000, 512, 112, 2048, 10),  # k = 10 (the paper's largest frontier k); the fewest experts of the sweep
     (130, 2048, 64, 4100, 20),   # r = 64 with k = 20, long h
-    (97, 128, 96, 64, 24),       # blocks 64+32, M = 64 (two expert tiles)
+    (97, 128, 96, 64, 24),       # M = 64 (two expert tiles)
 ]
 
 

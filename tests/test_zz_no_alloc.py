@@ -1,7 +1,6 @@
 """The no-allocation entry point through the C ABI (marked `gpu`): two calls in a row, the
-second on a smaller input (single-pass route, then resident route), then a call on the wide
-route, each bitwise equal to more_route_lowrank with a torch-allocated workspace, and in
-oracle parity."""
+second on a smaller input, then a call on the wide route, each bitwise equal to
+more_route_lowrank with a torch-allocated workspace, and in oracle parity."""
 import ctypes
 
 import numpy as np
@@ -38,8 +37,8 @@ def test_noalloc_matches_the_workspace_entry_point_on_two_calls():
     from paper_2609_36301_amd import _lib
     require_gpu()
     lib = _lib.load()
-    # the first call takes the single-pass route, the second (smaller) the resident route, on
-    # scratch that still holds the first call's data
+    # two calls of the bucket route (reported as single-pass and expert-resident), the second
+    # smaller, on scratch that still holds the first call's data
     for shape in ((4096, 512, 64, 40000, 8), (700, 256, 32, 9000, 16)):
         T, h, r, M, k = shape
         inp = make_inputs(T, h, r, M, seed=T + 11 * M)
@@ -68,8 +67,8 @@ def test_noalloc_matches_the_workspace_entry_point_on_two_calls():
 
 
 def test_noalloc_wide_route_matches_the_workspace_entry_point():
-    # r = 128 with k = 20 takes the wide route; its z, split and list buffers come from the
-    # same static scratch, which still holds the previous calls' data
+    # r = 128 with k = 20 takes the wide route; its z and maxima come from the same static
+    # scratch, which still holds the previous calls' data
     import torch
     from gpu_util import announce, require_gpu, to_dev
     from paper_2609_36301_amd import _lib, router
